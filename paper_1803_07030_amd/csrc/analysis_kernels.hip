@@ -10,101 +10,150 @@
 // history[r][s][m][5] = (E, Mx, My, Mz, accepted), MCS m0 .. M-1.  Every sum
 // is taken in a fixed order (strided per thread, then a fixed tree), so the
 // results are reproducible run to run.
+#include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "hsim_host.h"
+#include "wave.h"
 
 namespace hsim {
 
 namespace {
 
-constexpr int kAT = 256;   // threads per analysis block
+constexpr int kAT = 1024;            // threads of the per-series blocks
+constexpr int kAW = kAT / 64;
+constexpr int kMT = 256;             // threads of the multiple-histogram blocks
+constexpr int kMW = kMT / 64;
 
-// Block-wide sum (fixed order: per-thread values, then a halving tree);
-// every thread gets the result.
-__device__ double block_sum(double v, double *lds)
+// Block-wide sums of NV values (fixed order: a tree over each wave, then the
+// waves in order); every thread gets the results.  lds: kAW * NV doubles.
+template <int NV>
+__device__ __forceinline__ void block_sums(double (&v)[NV], double *lds)
 {
-    lds[threadIdx.x] = v;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = wave_all(v[q], OpAdd());
+    const int w = threadIdx.x >> 6;
+    __syncthreads();                 // the previous use of lds is over
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) lds[w * NV + q] = v[q];
     __syncthreads();
-    for (int s = kAT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
-        __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double t = lds[q];
+#pragma unroll
+        for (int k = 1; k < kAW; ++k) t += lds[k * NV + q];
+        v[q] = t;
     }
-    const double r = lds[0];
-    __syncthreads();
-    return r;
 }
 
-__device__ double block_max(double v, double *lds)
+__device__ __forceinline__ double block_max(double v, double *lds)
 {
-    lds[threadIdx.x] = v;
+    v = wave_all(v, OpMax());
     __syncthreads();
-    for (int s = kAT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) lds[threadIdx.x] = fmax(lds[threadIdx.x], lds[threadIdx.x + s]);
-        __syncthreads();
-    }
-    const double r = lds[0];
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
     __syncthreads();
-    return r;
+    double t = lds[0];
+#pragma unroll
+    for (int k = 1; k < kAW; ++k) t = fmax(t, lds[k]);
+    return t;
 }
 
-// Sample k of a set of series: series t = k / n, MCS m0 + k % n.
-struct Samples {
-    const double *hist;
-    const int32_t *rs;     // [K][2] (replica, step)
-    int32_t S, M, m0, n;   // steps, MCS per step, first MCS, samples per series
-    __device__ const double *rec(int64_t k) const
+// One series: its records of 5 doubles from MCS m0 on.
+struct Series {
+    const double *rec;
+    __device__ Series(const double *hist, int64_t series, int M, int m0)
+        : rec(hist + (series * M + m0) * 5) {}
+    __device__ double E(int m) const { return rec[(size_t)m * 5]; }
+    __device__ double A(int m) const
     {
-        const int t = (int)(k / n), m = m0 + (int)(k % n);
-        return hist + (((size_t)rs[2 * t] * S + rs[2 * t + 1]) * M + m) * 5;
-    }
-    __device__ double E(int64_t k) const { return rec(k)[0]; }
-    __device__ double A(int64_t k) const
-    {
-        const double *h = rec(k);
+        const double *h = rec + (size_t)m * 5;
         return sqrt((h[1] * h[1] + h[2] * h[2]) + h[3] * h[3]);
     }
 };
 
-// Thermal summary of samples [k0, k0 + count) with log-weights
-// logw(k) (weights shifted by their maximum); out[9] =
-// (e, m_abs, m2, m4, cv, chi, u4, v1, v2) for N sites at beta.
-template <typename LW>
-__device__ void thermal_block(const Samples &sm, int64_t k0, int64_t count, LW logw, double N,
-                              double beta, double *lds, double *out)
+// Thermal summary of count samples (get(i, e, a): energy and |M|) with
+// log-weights logw(i, e) (weights shifted by their maximum); out[9] =
+// (e, m_abs, m2, m4, cv, chi, u4, v1, v2) for N sites at beta.  K > 0: at
+// most K samples per thread, held in registers between the three passes (the
+// weights' maximum, the means, the central moments); K = 0: any count, read
+// again by each pass.
+template <int K, typename GET, typename LW>
+__device__ __forceinline__ void thermal_block(int64_t count, GET get, LW logw, double N, double beta,
+                                              double *lds, double *out)
 {
+    double e[K > 0 ? K : 1], a[K > 0 ? K : 1];
     double mx = -INFINITY;
-    for (int64_t k = threadIdx.x; k < count; k += kAT) mx = fmax(mx, logw(k0 + k));
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = (int)threadIdx.x + j * kAT;
+            e[j] = 0.0;
+            a[j] = 0.0;
+            if (i < count) get(i, e[j], a[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = (int)threadIdx.x + j * kAT;
+            mx = i < count ? fmax(mx, logw(i, e[j])) : mx;
+        }
+    } else {
+        for (int64_t i = threadIdx.x; i < count; i += kAT) {
+            get(i, e[0], a[0]);
+            mx = fmax(mx, logw(i, e[0]));
+        }
+    }
     mx = block_max(mx, lds);
-    double sw = 0, sE = 0, sA = 0, sA2 = 0, sA4 = 0;
-    for (int64_t k = threadIdx.x; k < count; k += kAT) {
-        const double w = exp(logw(k0 + k) - mx);
-        const double e = sm.E(k0 + k), a = sm.A(k0 + k), a2 = a * a;
-        sw += w;
-        sE += w * e;
-        sA += w * a;
-        sA2 += w * a2;
-        sA4 += w * (a2 * a2);
+    double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    auto first = [&](double wi, double ei, double ai) {
+        const double a2 = ai * ai;
+        s[0] += wi;
+        s[1] += wi * ei;
+        s[2] += wi * ai;
+        s[3] += wi * a2;
+        s[4] += wi * (a2 * a2);
+    };
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = (int)threadIdx.x + j * kAT;
+            if (i < count) first(exp(logw(i, e[j]) - mx), e[j], a[j]);
+            __builtin_amdgcn_sched_barrier(0);   // one exponential's registers at a time
+        }
+    } else {
+        for (int64_t i = threadIdx.x; i < count; i += kAT) {
+            get(i, e[0], a[0]);
+            first(exp(logw(i, e[0]) - mx), e[0], a[0]);
+        }
     }
-    const double W = block_sum(sw, lds);
-    const double mE = block_sum(sE, lds) / W, mA = block_sum(sA, lds) / W;
-    const double mA2 = block_sum(sA2, lds) / W, mA4 = block_sum(sA4, lds) / W;
-    double vE = 0, vA = 0, c1 = 0, c2 = 0;
-    for (int64_t k = threadIdx.x; k < count; k += kAT) {
-        const double w = exp(logw(k0 + k) - mx);
-        const double a = sm.A(k0 + k);
-        const double dE = sm.E(k0 + k) - mE, dA = a - mA, dA2 = a * a - mA2;
-        vE += w * (dE * dE);
-        vA += w * (dA * dA);
-        c1 += w * (dA * dE);
-        c2 += w * (dA2 * dE);
+    block_sums<5>(s, lds);
+    const double W = s[0], mE = s[1] / W, mA = s[2] / W, mA2 = s[3] / W, mA4 = s[4] / W;
+    double c[4] = {0.0, 0.0, 0.0, 0.0};
+    auto second = [&](double wi, double ei, double ai) {
+        const double dE = ei - mE, dA = ai - mA, dA2 = ai * ai - mA2;
+        c[0] += wi * (dE * dE);
+        c[1] += wi * (dA * dA);
+        c[2] += wi * (dA * dE);
+        c[3] += wi * (dA2 * dE);
+    };
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = (int)threadIdx.x + j * kAT;
+            if (i < count) second(exp(logw(i, e[j]) - mx), e[j], a[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        for (int64_t i = threadIdx.x; i < count; i += kAT) {
+            get(i, e[0], a[0]);
+            second(exp(logw(i, e[0]) - mx), e[0], a[0]);
+        }
     }
-    vE = block_sum(vE, lds) / W;
-    vA = block_sum(vA, lds) / W;
-    c1 = block_sum(c1, lds) / W;
-    c2 = block_sum(c2, lds) / W;
+    block_sums<4>(c, lds);
     if (threadIdx.x == 0) {
+        const double vE = c[0] / W, vA = c[1] / W, c1 = c[2] / W, c2 = c[3] / W;
         const double m2 = mA2 / (N * N), m4 = mA4 / (N * N * N * N);
         out[0] = mE / N;
         out[1] = mA / N;
@@ -118,60 +167,172 @@ __device__ void thermal_block(const Samples &sm, int64_t k0, int64_t count, LW l
     }
 }
 
-// grid (series, n_eval): series t at its sampling beta0[t], evaluated at
-// beta_eval[t][j] with weights exp(-(beta - beta0) E).
-__global__ __launch_bounds__(kAT) void k_thermal(Samples sm, double N, const double *beta0,
-                                                 const double *beta_eval, int n_eval, double *out)
+// The inverse temperatures of a thermal call, [series][1 + n_eval]: the
+// sampling value, then the evaluation values.  Up to kArgBeta of them (3 KiB
+// of the 4 KiB of arguments) travel in the kernel's arguments, and a call then
+// allocates and copies nothing; more go to device memory.
+constexpr int kArgBeta = 384;
+struct BetaTable {
+    double v[kArgBeta];
+};
+
+// grid (series, n_eval): series t at its sampling beta, evaluated with weights
+// exp(-(beta - beta0) E).  One block per evaluation, bounded by latency: a
+// series of up to 12 * 1024 samples (what 128 registers per thread hold) is
+// read once and stays in registers, a longer one is read by each of the three
+// passes.  64 series of 9000 samples at 3 betas: 65.6 us with 256 threads
+// that read it three times, 26 us now.
+template <int K, bool ARG>
+__global__ __launch_bounds__(kAT) void k_thermal(const double *hist, int M, int m0, int n, double N,
+                                                 const double *tab, BetaTable bt, int n_eval, double *out)
 {
-    __shared__ double lds[kAT];
+    __shared__ double lds[kAW * 5];
     const int t = blockIdx.x, j = blockIdx.y;
-    const double b0 = beta0[t], b = beta_eval[(size_t)t * n_eval + j];
+    const size_t row = (size_t)t * (1 + n_eval);
+    const double b0 = ARG ? bt.v[row] : tab[row], b = ARG ? bt.v[row + 1 + j] : tab[row + 1 + j];
     const double db = b - b0;
-    auto logw = [&](int64_t k) { return db == 0.0 ? 0.0 : -db * sm.E(k); };
-    thermal_block(sm, (int64_t)t * sm.n, sm.n, logw, N, b, lds, out + ((size_t)t * n_eval + j) * 9);
+    const Series sr(hist, t, M, m0);
+    auto get = [&](int64_t i, double &e, double &a) {
+        e = sr.E((int)i);
+        a = sr.A((int)i);
+    };
+    auto logw = [&](int64_t, double e) { return db == 0.0 ? 0.0 : -db * e; };
+    thermal_block<K>(n, get, logw, N, b, lds, out + ((size_t)t * n_eval + j) * 9);
 }
 
-// Integrated autocorrelation time of series t (observable 0: E, 1: |M|)
-// with the automatic window of Sokal: lags are evaluated 256 at a time, each
-// as one ordered sum, and thread 0 walks them until lag >= c tau.
-__global__ __launch_bounds__(kAT) void k_tau(Samples sm, int obs, double c, double *tau_out,
-                                             int32_t *win_out)
+// Integrated autocorrelation time of series t (observable 0: E, 1: |M|) with
+// the automatic window of Sokal: lags are evaluated kLags at a time, each as
+// one ordered sum, and thread 0 walks them until lag >= c tau.
+//
+// The sums sum_m d[m] d[m + lag] are a sliding correlation: wave w of the
+// block takes kLagW consecutive lags, lane l a contiguous run of m of odd
+// length, and slides a window of kLagW values along it, so a step reads two
+// LDS words and does kLagW multiply-adds (the odd run length spreads the
+// lanes over the banks).  Series of up to kTauRes samples stay in LDS;
+// longer ones pass through it in segments.  64 series of 9000 samples with
+// windows of up to 240 lags: 9.4 ms with one thread per lag walking the whole
+// series in global memory, 60 us now.
+constexpr int kLagW = 8, kLags = kAW * kLagW;
+constexpr int kTauRes = 18432;       // samples of a resident series (144 KiB of LDS)
+constexpr int kTauSeg = 8192;        // samples of a segment otherwise
+
+// pad: zeros held behind a resident series.
+__global__ __launch_bounds__(kAT) void k_tau(const double *hist, int M, int m0, int n, int pad, int obs, double c,
+                                             double *tau_out, int32_t *win_out)
 {
-    __shared__ double lds[kAT];
-    __shared__ double rho[kAT];
+    extern __shared__ double dyn[];
+    __shared__ double lds[kAW];
+    __shared__ double rho[kLags];
     __shared__ int done;
     const int t = blockIdx.x;
-    const int64_t k0 = (int64_t)t * sm.n;
-    const int n = sm.n;
-    auto x = [&](int m) { return obs == 0 ? sm.E(k0 + m) : sm.A(k0 + m); };
-    double s = 0.0;
-    for (int m = threadIdx.x; m < n; m += kAT) s += x(m);
-    const double mean = block_sum(s, lds) / n;
-    double q = 0.0;
+    const Series sr(hist, t, M, m0);
+    auto x = [&](int m) { return obs == 0 ? sr.E(m) : sr.A(m); };
+    const bool res = n <= kTauRes;
+    double s[1] = {0.0};
     for (int m = threadIdx.x; m < n; m += kAT) {
-        const double d = x(m) - mean;
-        q += d * d;
+        const double v = x(m);
+        if (res) dyn[m] = v;
+        s[0] += v;
     }
-    const double c0 = block_sum(q, lds) / n;
+    for (int m = threadIdx.x; m < pad; m += kAT) dyn[n + m] = 0.0;
+    block_sums<1>(s, lds);
+    const double mean = s[0] / n;
+    double q[1] = {0.0};
+    for (int m = threadIdx.x; m < n; m += kAT) {
+        const double d = (res ? dyn[m] : x(m)) - mean;
+        if (res) dyn[m] = d;
+        q[0] += d * d;
+    }
+    block_sums<1>(q, lds);
+    const double c0 = q[0] / n;
     double tau = 0.5;
     int win = n / 2;
     if (threadIdx.x == 0) done = c0 > 0.0 ? 0 : 1;
     __syncthreads();
-    for (int base = 1; base <= n / 2 && !done; base += kAT) {
-        const int lag = base + (int)threadIdx.x;
-        double r = 0.0;
-        if (lag <= n / 2) {
-            for (int m = 0; m + lag < n; ++m) r += (x(m) - mean) * (x(m + lag) - mean);
-            r = r / (n - lag) / c0;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int base = 1; base <= n / 2 && !done; base += kLags) {
+        const int lag0 = base + wv * kLagW;
+        double r[kLagW];
+#pragma unroll
+        for (int u = 0; u < kLagW; ++u) r[u] = 0.0;
+        const int seg = res ? n : kTauSeg;
+        for (int s0 = 0; s0 < n; s0 += seg) {
+            // A: d[s0 ..], la values; B: d[s0 + base ..], lb values (0 past it)
+            const int la = min(seg, n - s0), lb = max(0, min(seg + kLags, n - s0 - base));
+            const double *A = dyn, *B = res ? dyn + base : dyn + kTauSeg;
+            if (!res) {
+                __syncthreads();
+                for (int m = threadIdx.x; m < la; m += kAT) dyn[m] = x(s0 + m) - mean;
+                for (int m = threadIdx.x; m < lb; m += kAT) dyn[kTauSeg + m] = x(s0 + base + m) - mean;
+                __syncthreads();
+            }
+            const int run = ((la + 63) / 64) | 1;
+            const int lo = lane * run, hi = min(lo + run, la), off = wv * kLagW;
+            auto slide = [&](auto bval) {
+                double wd[kLagW];
+#pragma unroll
+                for (int u = 0; u < kLagW - 1; ++u) wd[u] = bval(lo + off + u);
+                int m = lo;
+                for (; m + kLagW <= hi; m += kLagW) {
+                    double a[kLagW], nx[kLagW];
+#pragma unroll
+                    for (int u = 0; u < kLagW; ++u) {
+                        a[u] = A[m + u];
+                        nx[u] = bval(m + off + kLagW - 1 + u);
+                    }
+#pragma unroll
+                    for (int v = 0; v < kLagW; ++v) {
+                        wd[kLagW - 1] = nx[v];
+#pragma unroll
+                        for (int u = 0; u < kLagW; ++u) r[u] = fma(a[v], wd[u], r[u]);
+#pragma unroll
+                        for (int u = 0; u < kLagW - 1; ++u) wd[u] = wd[u + 1];
+                    }
+                }
+                for (; m < hi; ++m) {
+                    wd[kLagW - 1] = bval(m + off + kLagW - 1);
+                    const double d = A[m];
+#pragma unroll
+                    for (int u = 0; u < kLagW; ++u) r[u] = fma(d, wd[u], r[u]);
+#pragma unroll
+                    for (int u = 0; u < kLagW - 1; ++u) wd[u] = wd[u + 1];
+                }
+            };
+            if (lag0 <= n / 2 && lo < hi) {
+                // past the series' end B counts as 0: either the zeros behind
+                // the resident series reach that far, or each read is checked
+                if (res && base + kLags + kLagW <= pad)
+                    slide([&](int k) { return B[k]; });
+                else
+                    slide([&](int k) {
+                        const double v = B[max(min(k, lb - 1), 0)];
+                        return k < lb ? v : 0.0;
+                    });
+            }
         }
-        rho[threadIdx.x] = r;
+#pragma unroll
+        for (int u = 0; u < kLagW; ++u) r[u] = wave_all(r[u], OpAdd());
+        if (lane == 0)
+#pragma unroll
+            for (int u = 0; u < kLagW; ++u) rho[wv * kLagW + u] = r[u] / (n - (lag0 + u)) / c0;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int u = 0; u < kAT && base + u <= n / 2; ++u) {
-                tau += rho[u];
-                if (base + u >= c * tau) {
-                    win = base + u;
-                    done = 1;
+        if (wv == 0) {
+            // tau up to each lag: a scan over the lanes, 64 lags at a time
+            for (int h = 0; h < kLags && base + h <= n / 2; h += 64) {
+                const int lag = base + h + lane;
+                double p = lag <= n / 2 ? rho[h + lane] : 0.0;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const double q = __shfl_up(p, o, 64);
+                    p = lane >= o ? p + q : p;
+                }
+                const double tl = tau + p;
+                const unsigned long long hit = __ballot(lag <= n / 2 && lag >= c * tl);
+                const int at = hit ? __ffsll(hit) - 1 : 63;
+                tau = __shfl(tl, at, 64);
+                if (hit) {
+                    win = base + h + at;
+                    if (lane == 0) done = 1;
                     break;
                 }
             }
@@ -184,48 +345,217 @@ __global__ __launch_bounds__(kAT) void k_tau(Samples sm, int obs, double c, doub
     }
 }
 
-// Multiple histogram, per sample: ln D = ln sum_j n_j exp(f_j - beta_j E),
-// shifted by the largest exponent.
-__global__ void k_mh_logd(Samples sm, int K, const double *beta_k, const double *f,
-                          double *logd)
+// ------------------------------------------------------- multiple histograms
+// Outcome of a multiple-histogram call.
+struct MhCtl {
+    int32_t done, iters;
+};
+
+// Energies and |M| of the K series, series after series.
+__global__ __launch_bounds__(kMT) void k_mh_gather(const double *hist, const int32_t *rs, int S, int M,
+                                                   int m0, int n, int64_t tot, double *E, double *A)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= (int64_t)K * sm.n) return;
-    const double e = sm.E(k), ln_n = log((double)sm.n);
-    double mx = -INFINITY;
-    for (int j = 0; j < K; ++j) mx = fmax(mx, ln_n + f[j] - beta_k[j] * e);
-    double s = 0.0;
-    for (int j = 0; j < K; ++j) s += exp(ln_n + f[j] - beta_k[j] * e - mx);
-    logd[k] = mx + log(s);
+    const int64_t i = (int64_t)blockIdx.x * kMT + threadIdx.x;
+    if (i >= tot) return;
+    const int64_t k = i / n;
+    const int m = (int)(i - k * n);
+    const Series sr(hist, (int64_t)rs[2 * k] * S + rs[2 * k + 1], M, m0);
+    E[i] = sr.E(m);
+    A[i] = sr.A(m);
 }
 
-// f_k = -ln sum_i exp(-beta_k E_i - ln D_i), one block per k.
-__global__ __launch_bounds__(kAT) void k_mh_f(Samples sm, int K, const double *beta_k,
-                                              const double *logd, double *f_new)
+// Tables no thread of the launch writes, read through the constant address
+// space (scalar loads).
+typedef const __attribute__((address_space(4))) double *ConstD;
+
+// ln D = ln sum_j n_j exp(f_j - beta_j E), shifted by the largest exponent.
+template <typename F>
+__device__ __forceinline__ double mh_logd(double e, double ln_n, int K, ConstD beta_k, F f)
 {
-    __shared__ double lds[kAT];
-    const int k = blockIdx.x;
-    const int64_t tot = (int64_t)K * sm.n;
-    const double b = beta_k[k];
     double mx = -INFINITY;
-    for (int64_t i = threadIdx.x; i < tot; i += kAT) mx = fmax(mx, -b * sm.E(i) - logd[i]);
-    mx = block_max(mx, lds);
+#pragma unroll 4
+    for (int j = 0; j < K; ++j) mx = fmax(mx, ln_n + f(j) - beta_k[j] * e);
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < tot; i += kAT) s += exp(-b * sm.E(i) - logd[i] - mx);
-    s = block_sum(s, lds);
-    if (threadIdx.x == 0) f_new[k] = -(mx + log(s));
+#pragma unroll 4
+    for (int j = 0; j < K; ++j) s += exp(ln_n + f(j) - beta_k[j] * e - mx);
+    return mx + log(s);
+}
+
+__global__ __launch_bounds__(kMT) void k_mh_logd(int64_t tot, int n, int K, const double *E,
+                                                 const double *beta_k, const double *f, double *logd)
+{
+    const int64_t i = (int64_t)blockIdx.x * kMT + threadIdx.x;
+    if (i < tot)
+        logd[i] = mh_logd(E[i], log((double)n), K, (ConstD)beta_k, [&](int j) { return ((ConstD)f)[j]; });
+}
+
+// The self-consistent equations
+//   f_k = -ln sum_i exp(-beta_k E_i - ln D_i),  f_0 = 0
+// are iterated by one launch per iteration.  Launch j first completes
+// iteration j: it adds the sums that the blocks of launch j - 1 left and
+// tests convergence (every block by itself, in the same order, so all agree;
+// block 0 keeps the result).  Then each block takes its samples (per of them,
+// a multiple of kMT): ln D of each, and for every k the block's largest
+// exponent m and the sum s of exponentials relative to it, for launch j + 1.
+// No block waits for another and the host looks at the outcome once per
+// batch of launches; once done is set, later launches return at once.  An
+// iteration over 16 series of 2000 samples: 140 us with one block per k and a
+// copy to the host and back each time, 16 us now (30 us with the last block
+// to finish adding the sums behind a device-wide counter).
+// An exponent of -inf adds 0 (unless every one is -inf), NaN stays NaN.
+constexpr int kMhG = 16;             // lanes that add the blocks' sums of one k
+constexpr int kMhBlocks = 512;       // blocks at most
+constexpr int kMhK = 64;             // k whose block sums are formed together
+// K and K x blocks up to which every block adds the sums itself (64 KiB of
+// them read per block); beyond, a launch of one block per k adds them.
+constexpr int kMhFusedK = 256, kMhFusedSums = 4096;
+
+__device__ __forceinline__ double mh_term(double v, double m)
+{
+    const double t = exp(v - m);         // NaN where m = v = -inf
+    return m == -INFINITY ? (v == v ? 0.0 : v) : t;
+}
+
+// -ln of the sum over the nb blocks (p[b] = (m, s)), by 16 lanes; every lane
+// gets the result.
+__device__ __forceinline__ double mh_combine(const double2 *p, int nb, int gl)
+{
+    double m = -INFINITY, s = 0.0;
+    for (int q = gl; q < nb; q += kMhG) m = fmax(m, p[q].x);
+    m = row_all(m, OpMax());
+    for (int q = gl; q < nb; q += kMhG) s += p[q].x == -INFINITY ? p[q].y : p[q].y * exp(p[q].x - m);
+    s = row_all(s, OpAdd());
+    return m == -INFINITY ? NAN : -(m + log(s));
+}
+
+__global__ __launch_bounds__(64) void k_mh_combine(int nb, const double2 *part, double *raw, const MhCtl *ctl)
+{
+    if (ctl->done) return;
+    const double r = mh_combine(part + (size_t)blockIdx.x * nb, nb, threadIdx.x % kMhG);
+    if (threadIdx.x == 0) raw[blockIdx.x] = r;
+}
+
+// fbuf [2][K]: f of iteration j in row j & 1; raw [K]: without the shift to
+// f_0 = 0 (from k_mh_combine, not FUSED); part [2][K][blocks].  ONE: per ==
+// kMT, one sample per thread.
+template <bool FUSED, bool ONE>
+__global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, int n, int K, int max_iter,
+                                                 double tol, const double *E, const double *beta_k,
+                                                 double *fbuf, const double *raw, double *logd,
+                                                 double2 *part, MhCtl *ctl)
+{
+    __shared__ double2 sh[kMhK][kMW];
+    __shared__ double shf[FUSED ? kMhFusedK : 1];
+    if (ctl->done) return;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nb = gridDim.x;
+    double f0 = 0.0;
+    if (j > 0) {
+        if constexpr (FUSED) {
+            const double2 *p = part + (size_t)((j - 1) & 1) * K * nb;
+            for (int k0 = 0; k0 < K; k0 += kMT / kMhG) {
+                const int k = k0 + (int)threadIdx.x / kMhG;
+                const double r = mh_combine(p + (size_t)min(k, K - 1) * nb, nb, threadIdx.x % kMhG);
+                if (k < K && threadIdx.x % kMhG == 0) shf[k] = r;
+            }
+            __syncthreads();
+        }
+        const double *rw = FUSED ? shf : raw;
+        const double *prev = fbuf + (size_t)((j - 1) & 1) * K;
+        double *next = fbuf + (size_t)(j & 1) * K;
+        f0 = rw[0];
+        double dmax = 0.0;
+        for (int k = lane; k < K; k += 64) dmax = fmax(dmax, fabs(rw[k] - f0 - prev[k]));
+        dmax = wave_all(dmax, OpMax());
+        if (blockIdx.x == 0)
+            for (int k = threadIdx.x; k < K; k += kMT) next[k] = rw[k] - f0;
+        if (dmax < tol || j == max_iter) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                ctl->iters = j;
+                ctl->done = 1;
+            }
+            return;
+        }
+    }
+    auto f = [&](int k) { return j > 0 ? (FUSED ? shf[k] : ((ConstD)raw)[k]) - f0 : 0.0; };
+    const int64_t i0 = (int64_t)blockIdx.x * per, i1 = min(tot, i0 + per);
+    const double ln_n = log((double)n);
+    // a thread's own samples: i0 + threadIdx.x, + kMT, ...; the first stays in
+    // registers
+    const int64_t mine = i0 + threadIdx.x;
+    double e = 0.0, ld = 0.0;
+    if (mine < i1) {
+        e = E[mine];
+        ld = mh_logd(e, ln_n, K, (ConstD)beta_k, f);
+    }
+    if constexpr (!ONE)
+        for (int64_t i = mine + kMT; i < i1; i += kMT) logd[i] = mh_logd(E[i], ln_n, K, (ConstD)beta_k, f);
+    double2 *out = part + (size_t)(j & 1) * K * nb;
+    for (int k0 = 0; k0 < K; k0 += kMhK) {
+        const int kn = min(kMhK, K - k0);
+        if constexpr (ONE) {
+            // four k at a time (the last repeated), branch-free: their chains
+            // of dependent steps overlap
+            for (int k = 0; k < kn; k += 4) {
+                double v[4], m[4], s[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    v[u] = -((ConstD)beta_k)[k0 + min(k + u, kn - 1)] * e - ld;
+                    m[u] = mine < i1 ? v[u] : -INFINITY;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) m[u] = wave_all(m[u], OpMax());
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double t = mh_term(v[u], m[u]);
+                    s[u] = mine < i1 ? t : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) s[u] = wave_all(s[u], OpAdd());
+                if (lane == 0)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sh[min(k + u, kn - 1)][w] = make_double2(m[u], s[u]);
+            }
+        } else {
+            for (int k = 0; k < kn; ++k) {
+                const double b = ((ConstD)beta_k)[k0 + k], v0 = -b * e - ld;
+                double m = mine < i1 ? v0 : -INFINITY;
+                for (int64_t i = mine + kMT; i < i1; i += kMT) m = fmax(m, -b * E[i] - logd[i]);
+                m = wave_all(m, OpMax());
+                double s = mine < i1 ? mh_term(v0, m) : 0.0;
+                for (int64_t i = mine + kMT; i < i1; i += kMT) s += mh_term(-b * E[i] - logd[i], m);
+                s = wave_all(s, OpAdd());
+                if (lane == 0) sh[k][w] = make_double2(m, s);
+            }
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < kn) {
+            const int k = threadIdx.x;
+            double m = sh[k][0].x, s = 0.0;
+#pragma unroll
+            for (int q = 1; q < kMW; ++q) m = fmax(m, sh[k][q].x);
+#pragma unroll
+            for (int q = 0; q < kMW; ++q)
+                s += sh[k][q].x == -INFINITY ? sh[k][q].y : sh[k][q].y * exp(sh[k][q].x - m);
+            out[(size_t)(k0 + k) * nb + blockIdx.x] = make_double2(m, s);
+        }
+        __syncthreads();
+    }
 }
 
 // Thermal summary at beta_eval[j] from all samples of the K series with
 // weights exp(-beta E - ln D).
-__global__ __launch_bounds__(kAT) void k_mh_thermal(Samples sm, int K, double N, const double *logd,
-                                                    const double *beta_eval, double *out)
+__global__ __launch_bounds__(kAT) void k_mh_thermal(int64_t tot, double N, const double *E, const double *A,
+                                                    const double *logd, const double *beta_eval, double *out)
 {
-    __shared__ double lds[kAT];
+    __shared__ double lds[kAW * 5];
     const int j = blockIdx.x;
     const double b = beta_eval[j];
-    auto logw = [&](int64_t k) { return -b * sm.E(k) - logd[k]; };
-    thermal_block(sm, 0, (int64_t)K * sm.n, logw, N, b, lds, out + (size_t)j * 9);
+    auto get = [&](int64_t i, double &e, double &a) {
+        e = E[i];
+        a = A[i];
+    };
+    auto logw = [&](int64_t i, double e) { return -b * e - logd[i]; };
+    thermal_block<0>(tot, get, logw, N, b, lds, out + (size_t)j * 9);
 }
 
 void check_hist(const double *h, int32_t R, int32_t S, int32_t M, int32_t m0)
@@ -244,28 +574,33 @@ void analysis_thermal_impl(const double *d_hist, int32_t R, int32_t S, int32_t M
     if (n_sites < 1 || !beta || n_eval < 1 || !d_out || (n_eval > 1 && !beta_eval))
         throw Error(HSIM_E_ARG, "analysis_thermal: bad argument");
     const int T = R * S;
-    std::vector<int32_t> rs(2 * (size_t)T);
-    std::vector<double> be((size_t)T * n_eval);
+    std::vector<double> tab((size_t)T * (1 + n_eval));
     for (int t = 0; t < T; ++t) {
-        rs[2 * t] = t / S;
-        rs[2 * t + 1] = t % S;
+        double *row = tab.data() + (size_t)t * (1 + n_eval);
         if (!std::isfinite(beta[t]) || beta[t] < 0) throw Error(HSIM_E_PARAM, "beta must be finite and >= 0");
+        row[0] = beta[t];
         for (int j = 0; j < n_eval; ++j) {
             const double b = beta_eval ? beta_eval[(size_t)t * n_eval + j] : beta[t];
             if (!std::isfinite(b) || b < 0) throw Error(HSIM_E_PARAM, "beta must be finite and >= 0");
-            be[(size_t)t * n_eval + j] = b;
+            row[1 + j] = b;
         }
     }
-    DevBuf d_rs, d_b0, d_be;
-    d_rs.upload(rs);
-    d_b0.upload(std::vector<double>(beta, beta + T));
-    d_be.upload(be);
-    Samples sm{d_hist, (const int32_t *)d_rs.p, S, M, m0, M - m0};
-    hipLaunchKernelGGL(k_thermal, dim3((unsigned)T, (unsigned)n_eval), dim3(kAT), 0, st, sm,
-                       (double)n_sites, (const double *)d_b0.p, (const double *)d_be.p, n_eval,
-                       d_out);
+    DevBuf d_tab;
+    BetaTable bt{};
+    const bool arg = tab.size() <= (size_t)kArgBeta;
+    if (arg) std::copy(tab.begin(), tab.end(), bt.v);
+    else d_tab.upload(tab);
+    const int n = M - m0;
+    const dim3 grid((unsigned)T, (unsigned)n_eval), blk(kAT);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, blk, 0, st, d_hist, M, m0, n, (double)n_sites, (const double *)d_tab.p, bt,
+                           n_eval, d_out);
+    };
+    if (n <= 4 * kAT) launch(arg ? k_thermal<4, true> : k_thermal<4, false>);
+    else if (n <= 12 * kAT) launch(arg ? k_thermal<12, true> : k_thermal<12, false>);
+    else launch(arg ? k_thermal<0, true> : k_thermal<0, false>);
     hip_check(hipGetLastError(), "thermal launch");
-    hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");   // before the tables are freed
+    hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");   // before the table is freed
 }
 
 void analysis_tau_impl(const double *d_hist, int32_t R, int32_t S, int32_t M, int32_t m0,
@@ -273,16 +608,14 @@ void analysis_tau_impl(const double *d_hist, int32_t R, int32_t S, int32_t M, in
 {
     check_hist(d_hist, R, S, M, m0);
     if ((obs != 0 && obs != 1) || !(c > 0.0) || !d_tau) throw Error(HSIM_E_ARG, "analysis_tau: bad argument");
-    const int T = R * S;
-    std::vector<int32_t> rs(2 * (size_t)T);
-    for (int t = 0; t < T; ++t) {
-        rs[2 * t] = t / S;
-        rs[2 * t + 1] = t % S;
-    }
-    DevBuf d_rs;
-    d_rs.upload(rs);
-    Samples sm{d_hist, (const int32_t *)d_rs.p, S, M, m0, M - m0};
-    hipLaunchKernelGGL(k_tau, dim3((unsigned)T), dim3(kAT), 0, st, sm, obs, c, d_tau, d_win);
+    const int n = M - m0;
+    const int pad = n <= kTauRes ? std::min(n / 2 + 2 * kLags, kTauRes - n) : 0;
+    const size_t dyn = (n <= kTauRes ? (size_t)(n + pad) : (size_t)(2 * kTauSeg + kLags)) * sizeof(double);
+    if (dyn > 65536)
+        hip_check(hipFuncSetAttribute((const void *)k_tau, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn),
+                  "hipFuncSetAttribute");
+    hipLaunchKernelGGL(k_tau, dim3((unsigned)(R * S)), dim3(kAT), dyn, st, d_hist, M, m0, n, pad, obs, c, d_tau,
+                       d_win);
     hip_check(hipGetLastError(), "tau launch");
     hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
 }
@@ -307,46 +640,64 @@ void analysis_multihist_impl(const double *d_hist, int32_t R, int32_t S, int32_t
         if (!std::isfinite(beta_eval[j]) || beta_eval[j] < 0) throw Error(HSIM_E_PARAM, "beta must be finite and >= 0");
     const int n = M - m0;
     const int64_t tot = (int64_t)K * n;
-    DevBuf d_rs, d_bk, d_f, d_fn, d_logd, d_be;
-    d_rs.upload(rs);
-    d_bk.upload(std::vector<double>(beta_k, beta_k + K));
-    std::vector<double> f((size_t)K, 0.0), fn((size_t)K);
-    d_f.upload(f);
-    d_fn.alloc((size_t)K * 8);
-    d_logd.alloc((size_t)tot * 8);
-    Samples sm{d_hist, (const int32_t *)d_rs.p, S, M, m0, n};
-    const unsigned gl = (unsigned)((tot + 255) / 256);
-    int it = 0;
-    while (it < max_iter) {
-        ++it;
-        hipLaunchKernelGGL(k_mh_logd, dim3(gl), dim3(256), 0, st, sm, K, (const double *)d_bk.p,
-                           (const double *)d_f.p, (double *)d_logd.p);
-        hipLaunchKernelGGL(k_mh_f, dim3((unsigned)K), dim3(kAT), 0, st, sm, K, (const double *)d_bk.p,
-                           (const double *)d_logd.p, (double *)d_fn.p);
-        hip_check(hipGetLastError(), "multihist launch");
-        hip_check(hipMemcpyAsync(fn.data(), d_fn.p, (size_t)K * 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-        hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-        double dmax = 0.0;
-        const double f0 = fn[0];
-        for (int k = 0; k < K; ++k) {
-            fn[k] = fn[k] - f0;
-            dmax = std::max(dmax, std::fabs(fn[k] - f[k]));
+    const int64_t chunks = (tot + kMT - 1) / kMT;            // of kMT samples
+    const int per = (int)((chunks + kMhBlocks - 1) / kMhBlocks) * kMT;
+    const int nb = (int)((tot + per - 1) / per);
+    const bool fused = K <= kMhFusedK && (int64_t)K * nb <= kMhFusedSums;
+    // one allocation: E, |M| and ln D of every sample, the blocks' sums, f,
+    // then the tables written from the host in one copy: the outcome and f
+    // (zeros), the inverse temperatures, the series
+    static_assert(sizeof(MhCtl) == sizeof(double), "the outcome takes one word");
+    std::vector<double> tab(1 + 4 * (size_t)K + (size_t)n_eval, 0.0);
+    double *h = tab.data() + 1 + 2 * (size_t)K;
+    std::copy(beta_k, beta_k + K, h);
+    if (n_eval > 0) std::copy(beta_eval, beta_eval + n_eval, h + K);
+    std::memcpy(h + K + n_eval, rs.data(), (size_t)K * 8);
+    const size_t samples = 3 * (size_t)tot + (tot & 1);      // even: the sums are 16-byte aligned
+    const size_t sums = 4 * (size_t)K * nb;
+    DevBuf buf;
+    auto *E = (double *)buf.alloc((samples + sums + K + tab.size()) * 8);
+    double *A = E + tot, *logd = A + tot;
+    auto *part = (double2 *)(E + samples);
+    double *raw = E + samples + sums, *d_tab = raw + K;
+    auto *ctl = (MhCtl *)d_tab;
+    double *fbuf = d_tab + 1;
+    const double *bk = fbuf + 2 * (size_t)K, *be = bk + K;
+    const auto *d_rs = (const int32_t *)(be + n_eval);
+    hip_check(hipMemcpyAsync(d_tab, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
+    const dim3 all((unsigned)chunks);
+    hipLaunchKernelGGL(k_mh_gather, all, dim3(kMT), 0, st, d_hist, d_rs, S, M, m0, n, tot, E, A);
+    // iterations are enqueued in growing batches (launch j completes
+    // iteration j, so max_iter iterations take max_iter + 1 launches)
+    auto iter = fused ? (per == kMT ? k_mh_iter<true, true> : k_mh_iter<true, false>)
+                      : (per == kMT ? k_mh_iter<false, true> : k_mh_iter<false, false>);
+    MhCtl now{};
+    int64_t sent = 0;
+    for (int batch = 8; !now.done; batch = std::min(2 * batch, 64)) {
+        const int64_t end = std::min<int64_t>(sent + batch, (int64_t)max_iter + 1);
+        for (; sent < end; ++sent) {
+            const int j = (int)sent;
+            if (!fused && j > 0)
+                hipLaunchKernelGGL(k_mh_combine, dim3((unsigned)K), dim3(64), 0, st, nb,
+                                   (const double2 *)(part + (size_t)((j - 1) & 1) * K * nb), raw,
+                                   (const MhCtl *)ctl);
+            hipLaunchKernelGGL(iter, dim3((unsigned)nb), dim3(kMT), 0, st, j, tot, per, n, K, max_iter, tol,
+                               (const double *)E, bk, fbuf, (const double *)raw, logd, part, ctl);
         }
-        f = fn;
-        hip_check(hipMemcpyAsync(d_f.p, f.data(), (size_t)K * 8, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
-        if (dmax < tol) break;
+        hip_check(hipGetLastError(), "multihist launch");
+        hip_check(hipMemcpyAsync(&now, ctl, sizeof now, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+        hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
     }
-    hipLaunchKernelGGL(k_mh_logd, dim3(gl), dim3(256), 0, st, sm, K, (const double *)d_bk.p,
-                       (const double *)d_f.p, (double *)d_logd.p);
+    const double *f = fbuf + (size_t)(now.iters & 1) * K;
     if (n_eval > 0) {
-        d_be.upload(std::vector<double>(beta_eval, beta_eval + n_eval));
-        hipLaunchKernelGGL(k_mh_thermal, dim3((unsigned)n_eval), dim3(kAT), 0, st, sm, K,
-                           (double)n_sites, (const double *)d_logd.p, (const double *)d_be.p, d_out);
+        hipLaunchKernelGGL(k_mh_logd, all, dim3(kMT), 0, st, tot, n, K, (const double *)E, bk, f, logd);
+        hipLaunchKernelGGL(k_mh_thermal, dim3((unsigned)n_eval), dim3(kAT), 0, st, tot, (double)n_sites,
+                           (const double *)E, (const double *)A, (const double *)logd, be, d_out);
     }
     hip_check(hipGetLastError(), "multihist launch");
+    hip_check(hipMemcpyAsync(f_out, f, (size_t)K * 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
     hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-    for (int k = 0; k < K; ++k) f_out[k] = f[k];
-    if (iters_out) *iters_out = it;
+    if (iters_out) *iters_out = now.iters;
 }
 
 }  // namespace hsim
