@@ -304,11 +304,19 @@ hsim_batch batch_create_impl(int32_t R, const hsim_plan *plans, uint64_t seed,
             // lattices fill the GPU.  Measured on SC L^3 x 64 replicas (us per
             // phase): L = 56: 45.8 (32), 54.8 (16); L = 48: 37.4 (32), 34.0
             // (16), 28.1 (8); L = 32: 17.6 (16), 12.6 (8), 11.9 (4); 16 sites
-            // per wave was never the best and is not used.  hsim_autotune
-            // may pick another of these shapes.
+            // per wave was never the best and is not used.  Spin sets beyond
+            // the last-level cache (256 MB) take 8 as well: shorter tiles keep
+            // the rows that the sites in flight share closer together in
+            // time (us per MCS, 32 | 8: L = 66 (221 MB) 162 | 165, 68 (241 MB)
+            // 223 | 193, 80 (393 MB) 394 | 350, 96 (679 MB) 611 | 579); the
+            // largest go back to 32 (L = 128, 1.6 GB: 1281 | 1365).
+            // hsim_autotune may pick another of these shapes.
+            const int64_t spin_bytes = 12 * max_n * b->Rp;
             const int cus = device_cus() > 0 ? device_cus() : 256;
             int spw = hsim::kRepSitesPerWave;
-            if (rep_phase_blocks(b, spw) < 2 * (int64_t)cus)
+            if (spin_bytes > ((int64_t)230 << 20) && spin_bytes < ((int64_t)1 << 30) && b->Rp % 64 == 0)
+                spw = 8;
+            else if (rep_phase_blocks(b, spw) < 2 * (int64_t)cus)
                 for (int cand : {8, 4})
                     if (cand < spw && cand % hsim::kRepSitesPerStep == 0) {
                         spw = cand;
