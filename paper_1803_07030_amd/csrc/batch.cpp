@@ -318,7 +318,7 @@ hsim_batch batch_create_impl(int32_t R, const hsim_plan *plans, uint64_t seed,
                 spw = 8;
             else if (rep_phase_blocks(b, spw) < 2 * (int64_t)cus)
                 for (int cand : {8, 4})
-                    if (cand < spw && cand % hsim::kRepSitesPerStep == 0) {
+                    if (cand < spw) {
                         spw = cand;
                         if (rep_phase_blocks(b, cand) >= 4 * (int64_t)cus) break;
                     }

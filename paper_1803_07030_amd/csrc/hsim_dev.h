@@ -19,14 +19,7 @@ constexpr int kFinThreads = 512;    // threads per block of the site-lane finish
 constexpr int kRepWaves = HSIM_REP_WAVES;                    // waves per replica-lane block
 constexpr int kRepSitesPerWave = HSIM_REP_SITES_PER_WAVE;    // sites per wave of a tile
 constexpr int kRepThreads = kRepWaves * 64;
-#ifndef HSIM_REP_SITES_PER_STEP
-#define HSIM_REP_SITES_PER_STEP 1
-#endif
-// sites whose loads a wave issues together (64-lane groups); divides the
-// sites per wave
-constexpr int kRepSitesPerStep = HSIM_REP_SITES_PER_STEP;
-static_assert(kRepSitesPerWave % kRepSitesPerStep == 0 && kRepSitesPerWave % 4 == 0,
-              "sites per wave must be a multiple of the sites per step and of 4");
+static_assert(kRepSitesPerWave % 4 == 0, "sites per wave must be a multiple of 4");
 constexpr int kMaxPersistentBlocks = 4096;   // barrier flags reserved in the workspace
 constexpr int kXBarLines = 48;   // the flag region's last lines: per-XCD barrier words (3 x 16)
 constexpr int kRepTile = kRepWaves * kRepSitesPerWave;   // sites per replica-lane tile (at most)
@@ -147,6 +140,12 @@ struct RepLaneArgs {
     // dispatch order: slot u of colour c (after the XCD split) runs tile
     // tord[tile_off[c] + u] of the class; NULL: tile u
     const int32_t *tord;
+};
+
+// One colour phase: its sites [cb, ce) and its tiles, tile0 .. tile0 + nt - 1
+// of all colours' tiles.
+struct RepPhase {
+    int32_t cb, ce, tile0, nt;
 };
 
 // XCD-aware bijection of [0, nt): blocks are dispatched round-robin over the

@@ -12,8 +12,7 @@
 //
 // A tile is kRepWaves * spw consecutive sites of one colour class (spw =
 // kRepSitesPerWave, or fewer for small lattices); wave w of the tile's block
-// takes spw of them in order (kRepSitesPerStep at a time with 64-lane
-// groups, two at a time with 32-lane groups).  Each XCD takes a contiguous
+// takes spw of them in order, half of them per group with 32-lane groups.  Each XCD takes a contiguous
 // range of a colour's tiles; inside it an optional order table starts tiles
 // one plane of the class apart together (large lattices).
 // Per-MCS history: every tile writes one record per replica; records are
@@ -53,6 +52,7 @@ __device__ __forceinline__ void accumulate(double (&acc)[6], bool ok, bool live,
 template <int KM, int FM, bool UNI = false>
 struct RepSite {
     float k, ex, ey, ez, nx, ny, nz;
+    RepSite() = default;
     template <typename T>
     __device__ __forceinline__ static T ld(const T *p, int64_t i)
     {
@@ -97,15 +97,15 @@ __device__ __forceinline__ void rep_trace(const RunArgs &ra, int r, uint32_t g, 
              1u << (orig & 31));
 }
 
-// Trial of site i for one lane: the random move, or (VAR_POL) the move of the
-// site's type, with the lane's replica width for the adaptive move; ad tells
+// Trial of a site of the given type for one lane: the random move, or
+// (VAR_POL) the type's move, with the lane's replica width for the adaptive move; ad tells
 // whether the move is adaptive (its accepts steer the width).  With VAR_XT
 // and spin norms the move acts on the direction and the trial gets the
 // site's length mu back.
 template <int VAR>
-__device__ __forceinline__ Trial32 rep_trial(const RepLaneArgs &a, const RunArgs &ra, int i,
-                                             uint32_t orig, uint32_t g, uint32_t rid, float sx,
-                                             float sy, float sz, float sigma, float mu, bool &ad)
+__device__ __forceinline__ Trial32 rep_trial(const RunArgs &ra, int type, uint32_t orig, uint32_t g,
+                                             uint32_t rid, float sx, float sy, float sz, float sigma,
+                                             float mu, bool &ad)
 {
     const uint4 w = draw(ra.seed, orig, g, rid, 0);
     ad = false;
@@ -113,7 +113,7 @@ __device__ __forceinline__ Trial32 rep_trial(const RepLaneArgs &a, const RunArgs
     if constexpr (!(VAR & VAR_POL)) {
         t = trial32(w);
     } else {
-        const SitePol pl = pick_policy(ra.pol.pol, ra.pol.param, ra.pol.cos_t, a.type ? a.type[i] : 0);
+        const SitePol pl = pick_policy(ra.pol.pol, ra.pol.param, ra.pol.cos_t, type);
         ad = pl.pol == POL_ADAPTIVE;
         if (pl.pol == POL_RANDOM) {
             t = trial32(w);
@@ -144,13 +144,22 @@ struct RepXt {
     }
 };
 
+// A lane's replica: its temperature and field at the step, its adaptive width
+// and the counter word of its random numbers.
+struct LanePar {
+    float beta, b, sigma;
+    uint32_t rid;
+};
+
 // Update site i for replica lane r (spin column r of the rows),
 // generic CSR row walk (rows of any degree).
 template <int KM, int FM, int VAR>
 __device__ __forceinline__ void rep_site_update(const RepLaneArgs &a, int i, int r, uint32_t g,
-                                                float beta, float b, uint32_t rid, bool active,
-                                                float sigma, const RunArgs &ra, double (&acc)[6])
+                                                const LanePar &lp, bool active, const RunArgs &ra,
+                                                double (&acc)[6], bool &nan)
 {
+    const float beta = lp.beta, b = lp.b, sigma = lp.sigma;
+    const uint32_t rid = lp.rid;
     const size_t plane = (size_t)a.cs;
     float *S = a.spins + r;
     const int32_t rb = a.rp[i], re = a.rp[i + 1];
@@ -170,14 +179,14 @@ __device__ __forceinline__ void rep_site_update(const RepLaneArgs &a, int i, int
     const float sx = S[oi], sy = S[plane + oi], sz = S[2 * plane + oi];
     bool ad;
     const RepXt<false> xt = (VAR & VAR_XT) ? RepXt<false>(a, i) : RepXt<false>();
-    const Trial32 t = rep_trial<VAR>(a, ra, i, a.orig[i], g, rid, sx, sy, sz, sigma, xt.mu, ad);
+    const Trial32 t = rep_trial<VAR>(ra, (VAR & VAR_POL) && a.type ? a.type[i] : 0, a.orig[i], g, rid, sx, sy, sz, sigma, xt.mu, ad);
     float dE = (KM == K_NONE) ? delta_e32_iso(sx, sy, sz, t, hx, hy, hz)
                               : delta_e32(sx, sy, sz, t, hx, hy, hz, sp.k, sp.ex, sp.ey, sp.ez);
     if constexpr ((VAR & VAR_XT) != 0)
         dE = fmaf(-xt.kc, cubic32(t.x, t.y, t.z) - cubic32(sx, sy, sz), dE);
     const bool ok = accept32(dE, beta, t.u) && active;
     acc[5] += (ok && ad) ? 1.0 : 0.0;
-    if (active && dE != dE) atomicOr(&ra.ctl->status, 1u);
+    nan = nan || (active && dE != dE);
     if (ok) {
         S[oi] = t.x;
         S[plane + oi] = t.y;
@@ -232,139 +241,110 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t rs, int32_t lane_b
                                           kSpinStorePolicy);
 }
 
-// kRepSitesPerStep sites of one 64-lane group at once, rows padded to MAXD:
-// all loads of the step are issued before any store (sites of one colour
-// class are never neighbours); the own rows are written back whole.  Row entries are wave-uniform scalar loads;
-// spin rows go through the buffer descriptors with the row in soffset.
+// One site of a 64-lane group, row padded to MAXD: row entries are
+// wave-uniform scalar loads, spin rows go through the buffer descriptors with
+// the row in soffset, and the own row is written back whole.  nan: set where
+// a live lane's energy change is NaN.
 template <int KM, int FM, int MAXD, int VAR>
-__device__ __forceinline__ void rep_step_uniform(const RepLaneArgs &a, const SpinPlanes &sp3,
-                                                 int i0, int ce, int r, uint32_t g, float beta,
-                                                 float b, uint32_t rid, bool active, float sigma,
-                                                 const RunArgs &ra, double (&acc)[6])
+__device__ __forceinline__ void rep_step_uniform(const RepLaneArgs &a, const SpinPlanes &sp3, int i, int r,
+                                                 uint32_t g, const LanePar &lp, bool active,
+                                                 const RunArgs &ra, double (&acc)[6], bool &nan)
 {
-    constexpr int NS = kRepSitesPerStep;
     const int32_t lane_b = r * 4;        // byte offset of this replica inside a row
-    float hx[NS], hy[NS], hz[NS], sx[NS], sy[NS], sz[NS];
-    int ic[NS];
-    bool valid[NS];
+    float hx = 0.0f, hy = 0.0f, hz = 0.0f;
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        valid[u] = i0 + u < ce;
-        ic[u] = valid[u] ? i0 + u : ce - 1;
-        hx[u] = 0.0f;
-        hy[u] = 0.0f;
-        hz[u] = 0.0f;
-#pragma unroll
-        for (int sl = 0; sl < MAXD; ++sl) {
-            const int32_t ob = cload(a.ell_col, ic[u] * MAXD + sl) * a.ss * 4;   // row byte offset
-            const float Jp = cload(a.ell_J, ic[u] * MAXD + sl);
-            hx[u] = fmaf(Jp, bload(sp3.x, lane_b, ob), hx[u]);
-            hy[u] = fmaf(Jp, bload(sp3.y, lane_b, ob), hy[u]);
-            hz[u] = fmaf(Jp, bload(sp3.z, lane_b, ob), hz[u]);
-        }
-        const int32_t oi = ic[u] * a.ss * 4;
-        sx[u] = bload(sp3.x, lane_b, oi);
-        sy[u] = bload(sp3.y, lane_b, oi);
-        sz[u] = bload(sp3.z, lane_b, oi);
+    for (int sl = 0; sl < MAXD; ++sl) {
+        const int32_t ob = cload(a.ell_col, i * MAXD + sl) * a.ss * 4;   // row byte offset
+        const float Jp = cload(a.ell_J, i * MAXD + sl);
+        hx = fmaf(Jp, bload(sp3.x, lane_b, ob), hx);
+        hy = fmaf(Jp, bload(sp3.y, lane_b, ob), hy);
+        hz = fmaf(Jp, bload(sp3.z, lane_b, ob), hz);
     }
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int i = ic[u];
-        const RepSite<KM, FM, true> sp(a, i);
-        const float fx = fmaf(b, sp.nx, hx[u]);
-        const float fy = fmaf(b, sp.ny, hy[u]);
-        const float fz = fmaf(b, sp.nz, hz[u]);
-        bool ad;
-        const RepXt<true> xt = (VAR & VAR_XT) ? RepXt<true>(a, i) : RepXt<true>();
-        const Trial32 t = rep_trial<VAR>(a, ra, i, cload(a.orig, i), g, rid, sx[u], sy[u], sz[u],
-                                         sigma, xt.mu, ad);
-        float dE = (KM == K_NONE) ? delta_e32_iso(sx[u], sy[u], sz[u], t, fx, fy, fz)
-                                  : delta_e32(sx[u], sy[u], sz[u], t, fx, fy, fz, sp.k, sp.ex,
-                                              sp.ey, sp.ez);
-        if constexpr ((VAR & VAR_XT) != 0)
-            dE = fmaf(-xt.kc, cubic32(t.x, t.y, t.z) - cubic32(sx[u], sy[u], sz[u]), dE);
-        const bool live = active && valid[u];
-        const bool ok = accept32(dE, beta, t.u) && live;
-        acc[5] += (ok && ad) ? 1.0 : 0.0;
-        if (live && dE != dE) atomicOr(&ra.ctl->status, 1u);
-        const int32_t oi = i * a.ss * 4;
-        // every live lane stores (the old value when rejected): whole rows
-        // reach memory faster than rows with holes while the spin set stays
-        // in the last-level cache; masked_store keeps the accepted moves
-        // only (fewer bytes once the rows stream from HBM).  Same values.
-        if (live && (ok || !a.masked_store)) {
-            bstore(sp3.x, lane_b, oi, ok ? t.x : sx[u]);
-            bstore(sp3.y, lane_b, oi, ok ? t.y : sy[u]);
-            bstore(sp3.z, lane_b, oi, ok ? t.z : sz[u]);
-        }
-        if constexpr ((VAR & VAR_TRACE) != 0)
-            if (ok) rep_trace(ra, r, g, cload(a.orig, i));
-        accumulate(acc, ok, live, dE, ok ? t.x : sx[u], ok ? t.y : sy[u], ok ? t.z : sz[u]);
+    const int32_t oi = i * a.ss * 4;
+    const float sx = bload(sp3.x, lane_b, oi), sy = bload(sp3.y, lane_b, oi), sz = bload(sp3.z, lane_b, oi);
+    const RepSite<KM, FM, true> sp(a, i);
+    hx = fmaf(lp.b, sp.nx, hx);
+    hy = fmaf(lp.b, sp.ny, hy);
+    hz = fmaf(lp.b, sp.nz, hz);
+    bool ad;
+    const RepXt<true> xt = (VAR & VAR_XT) ? RepXt<true>(a, i) : RepXt<true>();
+    const uint32_t orig = cload(a.orig, i);
+    const Trial32 t = rep_trial<VAR>(ra, (VAR & VAR_POL) && a.type ? cload(a.type, i) : 0, orig, g, lp.rid, sx,
+                                     sy, sz, lp.sigma, xt.mu, ad);
+    float dE = (KM == K_NONE) ? delta_e32_iso(sx, sy, sz, t, hx, hy, hz)
+                              : delta_e32(sx, sy, sz, t, hx, hy, hz, sp.k, sp.ex, sp.ey, sp.ez);
+    if constexpr ((VAR & VAR_XT) != 0)
+        dE = fmaf(-xt.kc, cubic32(t.x, t.y, t.z) - cubic32(sx, sy, sz), dE);
+    const bool ok = accept32(dE, lp.beta, t.u) && active;
+    acc[5] += (ok && ad) ? 1.0 : 0.0;
+    nan = nan || (active && dE != dE);
+    // every live lane stores (the old value when rejected): whole rows reach
+    // memory faster than rows with holes while the spin set stays in the
+    // last-level cache; masked_store keeps the accepted moves only (fewer
+    // bytes once the rows stream from HBM).  Same values.
+    if (active && (ok || !a.masked_store)) {
+        bstore(sp3.x, lane_b, oi, ok ? t.x : sx);
+        bstore(sp3.y, lane_b, oi, ok ? t.y : sy);
+        bstore(sp3.z, lane_b, oi, ok ? t.z : sz);
     }
+    if constexpr ((VAR & VAR_TRACE) != 0)
+        if (ok) rep_trace(ra, r, g, orig);
+    accumulate(acc, ok, active, dE, ok ? t.x : sx, ok ? t.y : sy, ok ? t.z : sz);
 }
 
-// Two sites of one lane group at once: all loads of both sites are issued
-// before either stores (sites of one colour class are never neighbours).
+// One site of a 32-lane group (the two groups of a wave have sites of their
+// own); accepted moves are stored.  The row and the site's parameters are
+// loaded together, then the spins the row names, without a branch in
+// between, so a site is two dependent loads deep: bound by latency, 16 waves
+// per CU.  Two sites at once, the second one's row read slot by slot behind a
+// bound check, took 10.4 us per colour phase of the core/shell ball; this
+// takes 8.2 us, and so did two or four sites at once without the check, or
+// the next site's row loaded a site ahead.
 template <int KM, int FM, int MAXD, int VAR>
-__device__ __forceinline__ void rep_pair_update(const RepLaneArgs &a, int i0, int ce, int r,
-                                                uint32_t g, float beta, float b, uint32_t rid,
-                                                bool active, float sigma, const RunArgs &ra,
-                                                double (&acc)[6])
+__device__ __forceinline__ void rep_step_group(const RepLaneArgs &a, const SpinPlanes &sp3, int i, int r,
+                                               uint32_t g, const LanePar &lp, bool active, const RunArgs &ra,
+                                               double (&acc)[6], bool &nan)
 {
-    const size_t plane = (size_t)a.cs;
-    float *S = a.spins + r;
-    float hx[2], hy[2], hz[2], sx[2], sy[2], sz[2];
-    int ic[2];
-    bool valid[2];
+    const int32_t lane_b = r * 4;
+    int32_t col[MAXD];
+    float Jp[MAXD];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        valid[u] = i0 + u < ce;
-        ic[u] = valid[u] ? i0 + u : ce - 1;
-        hx[u] = 0.0f;
-        hy[u] = 0.0f;
-        hz[u] = 0.0f;
+    for (int sl = 0; sl < MAXD; ++sl) col[sl] = a.ell_col[i * MAXD + sl];
 #pragma unroll
-        for (int sl = 0; sl < MAXD; ++sl) {
-            const size_t o = (size_t)a.ell_col[ic[u] * MAXD + sl] * a.ss;
-            const float Jp = valid[u] ? a.ell_J[ic[u] * MAXD + sl] : 0.0f;
-            hx[u] = fmaf(Jp, S[o], hx[u]);
-            hy[u] = fmaf(Jp, S[plane + o], hy[u]);
-            hz[u] = fmaf(Jp, S[2 * plane + o], hz[u]);
-        }
-        const size_t oi = (size_t)ic[u] * a.ss;
-        sx[u] = S[oi];
-        sy[u] = S[plane + oi];
-        sz[u] = S[2 * plane + oi];
+    for (int sl = 0; sl < MAXD; ++sl) Jp[sl] = a.ell_J[i * MAXD + sl];
+    const uint32_t orig = a.orig[i];
+    const int type = (VAR & VAR_POL) && a.type ? a.type[i] : 0;
+    const RepSite<KM, FM> sp(a, i);
+    const RepXt<false> xt = (VAR & VAR_XT) ? RepXt<false>(a, i) : RepXt<false>();
+    float hx = 0.0f, hy = 0.0f, hz = 0.0f;
+#pragma unroll
+    for (int sl = 0; sl < MAXD; ++sl) {
+        const int32_t ob = col[sl] * (a.ss * 4) + lane_b;
+        hx = fmaf(Jp[sl], bload(sp3.x, ob, 0), hx);
+        hy = fmaf(Jp[sl], bload(sp3.y, ob, 0), hy);
+        hz = fmaf(Jp[sl], bload(sp3.z, ob, 0), hz);
     }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int i = ic[u];
-        const RepSite<KM, FM> sp(a, i);
-        const float fx = fmaf(b, sp.nx, hx[u]);
-        const float fy = fmaf(b, sp.ny, hy[u]);
-        const float fz = fmaf(b, sp.nz, hz[u]);
-        bool ad;
-        const RepXt<false> xt = (VAR & VAR_XT) ? RepXt<false>(a, i) : RepXt<false>();
-        const Trial32 t = rep_trial<VAR>(a, ra, i, a.orig[i], g, rid, sx[u], sy[u], sz[u], sigma,
-                                         xt.mu, ad);
-        float dE = (KM == K_NONE) ? delta_e32_iso(sx[u], sy[u], sz[u], t, fx, fy, fz)
-                                  : delta_e32(sx[u], sy[u], sz[u], t, fx, fy, fz, sp.k, sp.ex,
-                                              sp.ey, sp.ez);
-        if constexpr ((VAR & VAR_XT) != 0)
-            dE = fmaf(-xt.kc, cubic32(t.x, t.y, t.z) - cubic32(sx[u], sy[u], sz[u]), dE);
-        const bool live = active && valid[u];
-        const bool ok = accept32(dE, beta, t.u) && live;
-        acc[5] += (ok && ad) ? 1.0 : 0.0;
-        if (live && dE != dE) atomicOr(&ra.ctl->status, 1u);
-        const size_t oi = (size_t)i * a.ss;
-        if (ok) {
-            S[oi] = t.x;
-            S[plane + oi] = t.y;
-            S[2 * plane + oi] = t.z;
-            if constexpr ((VAR & VAR_TRACE) != 0) rep_trace(ra, r, g, a.orig[i]);
-        }
-        accumulate(acc, ok, live, dE, ok ? t.x : sx[u], ok ? t.y : sy[u], ok ? t.z : sz[u]);
+    const int32_t oi = i * (a.ss * 4) + lane_b;
+    const float sx = bload(sp3.x, oi, 0), sy = bload(sp3.y, oi, 0), sz = bload(sp3.z, oi, 0);
+    hx = fmaf(lp.b, sp.nx, hx);
+    hy = fmaf(lp.b, sp.ny, hy);
+    hz = fmaf(lp.b, sp.nz, hz);
+    bool ad;
+    const Trial32 t = rep_trial<VAR>(ra, type, orig, g, lp.rid, sx, sy, sz, lp.sigma, xt.mu, ad);
+    float dE = (KM == K_NONE) ? delta_e32_iso(sx, sy, sz, t, hx, hy, hz)
+                              : delta_e32(sx, sy, sz, t, hx, hy, hz, sp.k, sp.ex, sp.ey, sp.ez);
+    if constexpr ((VAR & VAR_XT) != 0)
+        dE = fmaf(-xt.kc, cubic32(t.x, t.y, t.z) - cubic32(sx, sy, sz), dE);
+    const bool ok = accept32(dE, lp.beta, t.u) && active;
+    acc[5] += (ok && ad) ? 1.0 : 0.0;
+    nan = nan || (active && dE != dE);
+    if (ok) {
+        bstore(sp3.x, oi, 0, t.x);
+        bstore(sp3.y, oi, 0, t.y);
+        bstore(sp3.z, oi, 0, t.z);
+        if constexpr ((VAR & VAR_TRACE) != 0) rep_trace(ra, r, g, orig);
     }
+    accumulate(acc, ok, active, dE, ok ? t.x : sx, ok ? t.y : sy, ok ? t.z : sz);
 }
 
 template <int KM, int FM>
@@ -436,7 +416,7 @@ struct Lanes {
 // policies (the tile also records its accepted adaptive moves, field 6),
 // VAR_XT cubic anisotropy and spin norms.
 template <int KM, int FM, int W, int MAXD, int VAR = 0>
-__device__ __forceinline__ void rep_tile(const RepLaneArgs &a, int colour, int tile, int group,
+__device__ __forceinline__ void rep_tile(const RepLaneArgs &a, const RepPhase &ph, int tile, int group,
                                          uint32_t g, const RunArgs &ra, double *part,
                                          double *red)
 {
@@ -444,38 +424,28 @@ __device__ __forceinline__ void rep_tile(const RepLaneArgs &a, int colour, int t
     constexpr bool POL = (VAR & VAR_POL) != 0;
     constexpr int NQ = POL ? 6 : 5;
     const Lanes<W> L(group);
-    const int ce = a.cls_off[colour + 1];
-    const int wbase = a.cls_off[colour] + tile * (kRepWaves * a.spw) + L.w * a.spw;
+    const int ce = ph.ce;
+    const int wbase = ph.cb + tile * (kRepWaves * a.spw) + L.w * a.spw;
     const int base = wbase + L.sub * SPL;
     const bool active = L.r < a.R;
-    const uint32_t s_abs = g / (uint32_t)ra.M;
-    float beta = 0.0f, b = 0.0f, sigma = 0.0f;
-    uint32_t rid = 0;
-    if (active) {
-        const size_t sidx = (size_t)L.r * ra.S_hist + s_abs;
-        beta = (float)ra.beta[sidx];
-        b = (float)ra.bfield[sidx];
-        rid = a.rep_id[L.r];
-        if (POL && ra.pol.adaptive) sigma = (float)ra.sigma[L.r];
-    }
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if constexpr (MAXD > 0) {
-        const SpinPlanes sp3(a);
-        for (int j = 0; j < SPL && base + j < ce; j += (W == 64 ? kRepSitesPerStep : 2)) {
-            if constexpr (W == 64)
-                rep_step_uniform<KM, FM, MAXD, VAR>(a, sp3, base + j, ce, L.r, g, beta, b, rid,
-                                                    active, sigma, ra, acc);
-            else
-                rep_pair_update<KM, FM, MAXD, VAR>(a, base + j, ce, L.r, g, beta, b, rid, active,
-                                                   sigma, ra, acc);
-        }
-    } else {
-        for (int j = 0; j < SPL; ++j) {
-            const int i = base + j;
-            if (i >= ce) break;
-            rep_site_update<KM, FM, VAR>(a, i, L.r, g, beta, b, rid, active, sigma, ra, acc);
-        }
+    bool nan = false;
+    // lanes past the last replica read its parameters; nothing of them is kept
+    const int rr = active ? L.r : a.R - 1;
+    const size_t sidx = (size_t)rr * ra.S_hist + g / (uint32_t)ra.M;
+    const LanePar lp{(float)ra.beta[sidx], (float)ra.bfield[sidx],
+                     POL && ra.pol.adaptive ? (float)ra.sigma[rr] : 0.0f, a.rep_id[rr]};
+    const SpinPlanes sp3(a);
+    for (int j = 0; j < SPL && base + j < ce; ++j) {
+        const int i = base + j;
+        if constexpr (MAXD == 0)
+            rep_site_update<KM, FM, VAR>(a, i, L.r, g, lp, active, ra, acc, nan);
+        else if constexpr (W == 64)
+            rep_step_uniform<KM, FM, MAXD, VAR>(a, sp3, i, L.r, g, lp, active, ra, acc, nan);
+        else
+            rep_step_group<KM, FM, MAXD, VAR>(a, sp3, i, L.r, g, lp, active, ra, acc, nan);
     }
+    if (nan) atomicOr(&ra.ctl->status, 1u);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) red[(L.w * 64 + L.lane) * NQ + q] = acc[q];
     __syncthreads();
@@ -488,7 +458,7 @@ __device__ __forceinline__ void rep_tile(const RepLaneArgs &a, int colour, int t
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) v[q] += red[(ww * 64 + sb * W + (int)threadIdx.x) * NQ + q];
         const int rr = (int)threadIdx.x + W * group;
-        const int tg = a.tile_off[colour] + tile;
+        const int tg = ph.tile0 + tile;
 #pragma unroll
         for (int q = 0; q < 5; ++q) part[((size_t)tg * kRecFields + q) * a.Rp + rr] = v[q];
         if constexpr (POL) part[((size_t)tg * kRecFields + 6) * a.Rp + rr] = v[5];
@@ -659,16 +629,26 @@ __device__ __forceinline__ double *rep_chunk_slot(const RunArgs &ra, const RepLa
 }
 
 // Per-phase kernel: grid (tiles of the colour, replica groups).
+//
+// On small lattices a launch is a chain of dependent loads (the kernel's
+// arguments, the MCS number and the tables, the temperatures and spins), so
+// the arguments a tile needs are fetched in one go: the empty asm takes them
+// all, and with it the compiler issues their scalar loads together instead of
+// one round after the other where each is first used.
 template <int KM, int FM, int W, int MAXD, int VAR>
-__global__ __launch_bounds__(kRepThreads) void k_rep_phase(RepLaneArgs a, int colour, int t_off,
-                                                           int ntiles, RunArgs ra)
+__global__ __launch_bounds__(kRepThreads) void k_rep_phase(RepPhase ph, int t_off, int ntiles, RepLaneArgs a,
+                                                           RunArgs ra)
 {
     __shared__ double red[kRedDoubles];
-    const uint32_t g = ra.ctl->g + (uint32_t)t_off;
-    const int nt = a.tile_off[colour + 1] - a.tile_off[colour];
-    const int u = xcd_tile(blockIdx.x, nt);
-    rep_tile<KM, FM, W, MAXD, VAR>(a, colour, a.tord ? a.tord[a.tile_off[colour] + u] : u, blockIdx.y, g,
-                                   ra, rep_slot(ra, a, ntiles, t_off % ra.rec_win), red);
+    asm volatile("" ::"s"(ph.cb), "s"(ph.ce), "s"(ph.tile0), "s"(ph.nt), "s"(t_off), "s"(ntiles), "s"(a.ell_col),
+                 "s"(a.ell_J), "s"(a.orig), "s"(a.spins), "s"(a.rep_id), "s"(a.cs), "s"(a.n), "s"(a.Rp), "s"(a.R),
+                 "s"(a.ss), "s"(a.spw), "s"(a.masked_store), "s"(a.tord), "s"(ra.ctl), "s"(ra.beta),
+                 "s"(ra.bfield), "s"(ra.partials), "s"(ra.seed), "s"(ra.M), "s"(ra.S_hist), "s"(ra.rec_win));
+    if constexpr (KM == K_SITE) asm volatile("" ::"s"(a.k), "s"(a.ax));
+        const uint32_t g = cload(&ra.ctl->g, 0) + (uint32_t)t_off;   // (no launch of the sweep writes it)
+    const int u = xcd_tile(blockIdx.x, ph.nt);
+    rep_tile<KM, FM, W, MAXD, VAR>(a, ph, a.tord ? cload(a.tord, ph.tile0 + u) : u, blockIdx.y, g, ra,
+                                   rep_slot(ra, a, ntiles, t_off % ra.rec_win), red);
 }
 
 // Adaptive widths after MCS t_off of the sequence: the accepted adaptive
@@ -982,9 +962,10 @@ __global__ __launch_bounds__(kRepThreads) void k_rep_persistent(RepLaneArgs a, i
         }
         for (int c = 0; c < a.ncol; ++c) {
             const int nt = a.tile_off[c + 1] - a.tile_off[c];
+            const RepPhase ph{a.cls_off[c], a.cls_off[c + 1], a.tile_off[c], nt};
             for (XcdRange it(nt * groups, xb); it.u < it.end; it.u += it.step) {
                 const int u = it.u % nt;
-                rep_tile<KM, FM, W, MAXD>(a, c, a.tord ? a.tord[a.tile_off[c] + u] : u, it.u / nt, g, ra,
+                rep_tile<KM, FM, W, MAXD>(a, ph, a.tord ? a.tord[ph.tile0 + u] : u, it.u / nt, g, ra,
                                           part, red);
             }
             xcd_barrier(ra.ctl, xb, epoch, cap);
@@ -1093,6 +1074,7 @@ hipError_t launch_rep_phase(hipStream_t st, int kmode, int fmode, int colour, in
 {
     const int nt = a.tile_off[colour + 1] - a.tile_off[colour];
     if (nt <= 0) return hipSuccess;
+    const RepPhase ph{a.cls_off[colour], a.cls_off[colour + 1], a.tile_off[colour], nt};
     const int Wd = lane_width(a);
     dim3 grid((unsigned)nt, (unsigned)(a.Rp / Wd));
     dim3 blk(kRepThreads);
@@ -1100,21 +1082,14 @@ hipError_t launch_rep_phase(hipStream_t st, int kmode, int fmode, int colour, in
         const int var = (ra.pol.n_types > 0 ? VAR_POL : 0) | (a.kc || a.mu ? VAR_XT : 0) |
                         (ra.trace ? VAR_TRACE : 0);
         if ((var & VAR_TRACE) && var != VAR_TRACE) return hipErrorInvalidValue;
-        if (var == VAR_TRACE)
-            hipLaunchKernelGGL((k_rep_phase<KM, FM, W, MAXD, VAR_TRACE>), grid, blk, 0, st, a,
-                               colour, t_off, ntiles, ra);
-        else if (var == 0)
-            hipLaunchKernelGGL((k_rep_phase<KM, FM, W, MAXD, 0>), grid, blk, 0, st, a, colour,
-                               t_off, ntiles, ra);
-        else if (var == VAR_POL)
-            hipLaunchKernelGGL((k_rep_phase<KM, FM, W, MAXD, VAR_POL>), grid, blk, 0, st, a, colour,
-                               t_off, ntiles, ra);
-        else if (var == VAR_XT)
-            hipLaunchKernelGGL((k_rep_phase<KM, FM, W, MAXD, VAR_XT>), grid, blk, 0, st, a, colour,
-                               t_off, ntiles, ra);
-        else
-            hipLaunchKernelGGL((k_rep_phase<KM, FM, W, MAXD, VAR_POL | VAR_XT>), grid, blk, 0, st,
-                               a, colour, t_off, ntiles, ra);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, blk, 0, st, ph, t_off, ntiles, a, ra);
+        };
+        if (var == VAR_TRACE) go(k_rep_phase<KM, FM, W, MAXD, VAR_TRACE>);
+        else if (var == 0) go(k_rep_phase<KM, FM, W, MAXD, 0>);
+        else if (var == VAR_POL) go(k_rep_phase<KM, FM, W, MAXD, VAR_POL>);
+        else if (var == VAR_XT) go(k_rep_phase<KM, FM, W, MAXD, VAR_XT>);
+        else go(k_rep_phase<KM, FM, W, MAXD, VAR_POL | VAR_XT>);
     }));
     return hipGetLastError();
 }
