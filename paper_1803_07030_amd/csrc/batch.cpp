@@ -755,13 +755,22 @@ struct PhaseTimer {
     }
 };
 
-// Site layout: MCS t_off = 0..count-1 of a launch sequence starting at
-// ctl->g (efull, colour phases, per-MCS reduction), then ctl->g moves on.
+// Which MCS of a launch sequence end a step: the host knows it from the
+// sequence's first MCS gb (plain launches), or the device checks every MCS
+// from `from` on (captured graphs, whose first MCS differs per replay).
+struct StepEnd {
+    uint32_t gb;
+    bool dev_check;
+    int from;
+    bool may_end(int t, int M) const
+    {
+        return dev_check ? t >= from : (gb + (uint32_t)t + 1) % (uint32_t)M == 0;
+    }
+};
+
 // Optional outputs after MCS t of a sequence: per-type magnetisation; the
-// spins at a step end, which the host knows from the sequence's first MCS gb
-// (plain launches) or the device checks (dev_check: captured graphs).
-void enqueue_outputs(hsim_batch b, const hsim::RunArgs &ra, int t, uint32_t gb, bool dev_check,
-                     hipStream_t st)
+// spins at a step end.
+void enqueue_outputs(hsim_batch b, const hsim::RunArgs &ra, int t, const StepEnd &ends, hipStream_t st)
 {
     const bool rep = b->layout == HSIM_LAYOUT_REPLICA;
     const auto *reps = (const hsim::RepDesc *)b->d_reps.p;
@@ -769,9 +778,9 @@ void enqueue_outputs(hsim_batch b, const hsim::RunArgs &ra, int t, uint32_t gb, 
         if (rep) hip_check(hsim::launch_type_mag_rep(st, b->la, t, ra), "type launch");
         else hip_check(hsim::launch_type_mag_site(st, b->f64, reps, b->R, ra.snap_n, t, ra), "type launch");
     }
-    if (b->snapshots && (dev_check || (gb + (uint32_t)t + 1) % (uint32_t)ra.M == 0)) {
-        if (rep) hip_check(hsim::launch_snapshot_rep(st, b->la, t, dev_check, ra), "snapshot launch");
-        else hip_check(hsim::launch_snapshot_site(st, b->f64, reps, b->R, ra.snap_n, t, dev_check, ra),
+    if (b->snapshots && ends.may_end(t, ra.M)) {
+        if (rep) hip_check(hsim::launch_snapshot_rep(st, b->la, t, ends.dev_check, ra), "snapshot launch");
+        else hip_check(hsim::launch_snapshot_site(st, b->f64, reps, b->R, ra.snap_n, t, ends.dev_check, ra),
                        "snapshot launch");
     }
 }
@@ -809,12 +818,9 @@ void enqueue_site_mcs(hsim_batch b, const hsim::RunArgs &ra, int g, int t, F efu
 // groups run their sequences on the batch's two streams, forked from st and
 // joined back into it (also inside a capture, where the fork and join become
 // graph edges); otherwise both groups' launches go to st, MCS by MCS.
-// Optional outputs after MCS t of a sequence: per-type magnetisation; the
-// spins at a step end, which the host knows from the sequence's first MCS gb
-// (plain launches) or the device checks (dev_check: captured graphs).
 template <typename F>
 void enqueue_site_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F efull_mask,
-                           hipStream_t st, uint32_t gb, bool dev_check, bool split)
+                           hipStream_t st, const StepEnd &ends, bool split)
 {
     if (count <= 0) return;
     if (split && b->ngroups > 1) {
@@ -835,7 +841,7 @@ void enqueue_site_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F e
     } else {
         for (int t = 0; t < count; ++t) {
             for (int g = 0; g < b->ngroups; ++g) enqueue_site_mcs(b, ra, g, t, efull_mask, st);
-            enqueue_outputs(b, ra, t, gb, dev_check, st);
+            enqueue_outputs(b, ra, t, ends, st);
         }
     }
     hip_check(hsim::launch_ctl_advance(st, ra.ctl, (uint32_t)count), "control launch");
@@ -848,7 +854,7 @@ void enqueue_site_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F e
 // recompute.
 template <typename F>
 void enqueue_rep_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F efull_mask,
-                          hipStream_t st, uint32_t gb, bool dev_check)
+                          hipStream_t st, const StepEnd &ends)
 {
     const int W = b->rec_win;
     for (int t = 0; t < count; ++t) {
@@ -863,7 +869,7 @@ void enqueue_rep_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F ef
         }
         if (ra.pol.adaptive)
             hip_check(hsim::launch_rep_sigma(st, b->la, b->rep_ntiles, t, ra), "sigma launch");
-        enqueue_outputs(b, ra, t, gb, dev_check, st);
+        enqueue_outputs(b, ra, t, ends, st);
         if ((t + 1) % W == 0 || t == count - 1) {
             const int first = t - t % W;
             hip_check(hsim::launch_rep_reduce(st, b->la, b->rep_ntiles, first, t - first + 1,
@@ -897,8 +903,9 @@ void run_plain(hsim_batch b, const hsim::RunArgs &ra, hipStream_t st, int from, 
     // ctl->g is at g0 + from here
     const uint32_t gb = ra.g0 + (uint32_t)from;
     auto mask = [&](int t) { return due(gb + (uint32_t)t, ra.M, ra.P); };
-    if (b->layout == HSIM_LAYOUT_REPLICA) enqueue_rep_sequence(b, ra, to - from, mask, st, gb, false);
-    else enqueue_site_sequence(b, ra, to - from, mask, st, gb, false, split_ok(b, st, false));
+    const StepEnd ends{gb, false, 0};
+    if (b->layout == HSIM_LAYOUT_REPLICA) enqueue_rep_sequence(b, ra, to - from, mask, st, ends);
+    else enqueue_site_sequence(b, ra, to - from, mask, st, ends, split_ok(b, st, false));
 }
 
 // Whether work enqueued on st is being recorded into a caller's graph.
@@ -910,11 +917,15 @@ bool capturing(hipStream_t st)
     return cs != hipStreamCaptureStatusNone;
 }
 
-// GRAPH mode: one recompute period (U MCS) captured once and replayed; the
-// instantiated graph stays on the batch while its captured arguments stay the
-// same (rebinding, new policies or outputs drop it).  Nothing synchronises:
-// the capture runs on a private stream where nothing executes, and the
-// replays are enqueued on the caller's stream.
+// GRAPH mode: U MCS captured once and replayed; the instantiated graph stays
+// on the batch while its captured arguments stay the same (rebinding, new
+// policies or outputs drop it).  U is a recompute period where periods tile a
+// step, else a whole step of up to 512 MCS: either way a replay's first MCS
+// fixes which of its MCS recompute the energy, so no others get a launch that
+// would find nothing due (1.3 - 4.7 us each).  Longer steps go in pieces of
+// 64 MCS whose recompute and step-end launches test the MCS on the device.
+// Nothing synchronises: the capture runs on a private stream where nothing
+// executes, and the replays are enqueued on the caller's stream.
 void run_graph(hsim_batch b, const hsim::RunArgs &ra, hipStream_t st)
 {
     const int total = ra.n_mcs_run;
@@ -923,12 +934,13 @@ void run_graph(hsim_batch b, const hsim::RunArgs &ra, hipStream_t st)
         return;
     }
     int U;
-    bool efull_each;
+    bool efull_each = false;
     if (ra.P > 0 && ra.M % ra.P == 0 && ra.P <= 512) {
         U = ra.P;
-        efull_each = false;
+    } else if (ra.M <= 512) {
+        U = ra.M;
     } else {
-        U = std::min(ra.M, 64);
+        U = 64;
         efull_each = true;
     }
     const int reps = total / U;
@@ -957,9 +969,10 @@ void run_graph(hsim_batch b, const hsim::RunArgs &ra, hipStream_t st)
         hipGraph_t graph = nullptr;
         hip_check(hipStreamBeginCapture(b->g_cap, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
         try {
-            auto mask = [&](int t) { return efull_each || t == 0; };
-            if (b->layout == HSIM_LAYOUT_REPLICA) enqueue_rep_sequence(b, rc, U, mask, b->g_cap, 0, true);
-            else enqueue_site_sequence(b, rc, U, mask, b->g_cap, 0, true, split_ok(b, b->g_cap, true));
+            auto mask = [&](int t) { return efull_each || t == 0 || (ra.P > 0 && t % ra.P == 0); };
+            const StepEnd ends{0, true, efull_each ? 0 : U - 1};
+            if (b->layout == HSIM_LAYOUT_REPLICA) enqueue_rep_sequence(b, rc, U, mask, b->g_cap, ends);
+            else enqueue_site_sequence(b, rc, U, mask, b->g_cap, ends, split_ok(b, b->g_cap, true));
         } catch (...) {
             (void)hipStreamEndCapture(b->g_cap, &graph);
             if (graph) (void)hipGraphDestroy(graph);
