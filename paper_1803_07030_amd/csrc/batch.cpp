@@ -460,6 +460,11 @@ void hsim_batch_s::upload_tables()
         la.ncol = P->ncol;
         la.ell_w = P->ell_w;
         for (int c = 0; c <= P->ncol; ++c) la.cls_off[c] = P->cls_off[c];
+        if (type_mag) {
+            drop_graph();
+            hip_check(hipDeviceSynchronize(), "hipDeviceSynchronize");   // enqueued launches read the old tables
+            build_type_sums();
+        }
         if (tord.empty()) la.tord = nullptr;
         else {
             d_tord.upload(tord);
@@ -624,12 +629,44 @@ void batch_bind_outputs_impl(hsim_batch b, int32_t n_types, double *type_mag, do
     b->snapshots = snapshots;
     b->tm_types = type_mag ? n_types : 0;
     b->d_tm_part.release();
-    if (type_mag) {
+    if (type_mag && b->layout == HSIM_LAYOUT_REPLICA) {
+        b->build_type_sums();
+    } else if (type_mag) {
         int64_t mn = 0;
         for (auto p : b->plans) mn = std::max(mn, p->n);
-        const int nblk = hsim::type_part_blocks(b->layout == HSIM_LAYOUT_REPLICA, (int)mn);
-        b->d_tm_part.alloc((size_t)b->R * nblk * n_types * 3 * 8);
+        b->d_tm_part.alloc((size_t)b->R * hsim::type_part_blocks((int)mn) * n_types * 3 * 8);
     }
+}
+
+// Replica layout: the sites type after type (internal order inside a type; a
+// type past tm_types is left out), cut into chunks of about 1/512 of the
+// lattice, at least 16 sites (a chunk is a block: two blocks per CU, and
+// still a few sites per lane group on small lattices), and the chunk sums of
+// a window of 1 to 64 MCS, 16 MiB at most.
+void hsim_batch_s::build_type_sums()
+{
+    hsim_plan P = plans[0];
+    const int64_t n = P->n, len = std::max<int64_t>(16, (n + 511) / 512);
+    std::vector<int32_t> list, chunk;
+    tsums = hsim::TypeSums{};
+    for (int t = 0; t < hsim::kMaxTypes; ++t) {
+        tsums.first[t] = (int32_t)chunk.size();
+        if (t >= tm_types) continue;
+        const size_t b0 = list.size();
+        for (int64_t i = 0; i < n; ++i)
+            if ((P->type.empty() ? 0 : P->type[i]) == t) list.push_back((int32_t)i);
+        for (size_t k = b0; k < list.size(); k += (size_t)len) chunk.push_back((int32_t)k);
+    }
+    tsums.first[hsim::kMaxTypes] = tsums.nchunk = (int32_t)chunk.size();
+    chunk.push_back((int32_t)list.size());
+    const size_t nc = chunk.size();
+    chunk.insert(chunk.end(), list.begin(), list.end());
+    const int32_t *d = d_tm_sites.upload(chunk);
+    tsums.chunk = d;
+    tsums.list = d + nc;
+    const size_t per_mcs = std::max<size_t>((size_t)tsums.nchunk * 3 * Rp * 8, 1);
+    tsums.win = (int32_t)std::max<size_t>(1, std::min<size_t>(64, (16u << 20) / per_mcs));
+    tsums.part = (double *)d_tm_part.alloc(per_mcs * tsums.win);
 }
 
 void batch_sigma_impl(hsim_batch b, double *out)
@@ -775,7 +812,7 @@ void enqueue_outputs(hsim_batch b, const hsim::RunArgs &ra, int t, const StepEnd
     const bool rep = b->layout == HSIM_LAYOUT_REPLICA;
     const auto *reps = (const hsim::RepDesc *)b->d_reps.p;
     if (b->type_mag) {
-        if (rep) hip_check(hsim::launch_type_mag_rep(st, b->la, t, ra), "type launch");
+        if (rep) hip_check(hsim::launch_type_sums_rep(st, b->la, b->tsums, t), "type launch");
         else hip_check(hsim::launch_type_mag_site(st, b->f64, reps, b->R, ra.snap_n, t, ra), "type launch");
     }
     if (b->snapshots && ends.may_end(t, ra.M)) {
@@ -870,6 +907,10 @@ void enqueue_rep_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F ef
         if (ra.pol.adaptive)
             hip_check(hsim::launch_rep_sigma(st, b->la, b->rep_ntiles, t, ra), "sigma launch");
         enqueue_outputs(b, ra, t, ends, st);
+        if (b->type_mag && ((t + 1) % b->tsums.win == 0 || t == count - 1)) {
+            const int first = t - t % b->tsums.win;
+            hip_check(hsim::launch_type_final_rep(st, b->la, b->tsums, first, t - first + 1, ra), "type launch");
+        }
         if ((t + 1) % W == 0 || t == count - 1) {
             const int first = t - t % W;
             hip_check(hsim::launch_rep_reduce(st, b->la, b->rep_ntiles, first, t - first + 1,

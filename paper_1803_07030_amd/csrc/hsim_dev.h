@@ -142,6 +142,17 @@ struct RepLaneArgs {
     const int32_t *tord;
 };
 
+// Replica layout, per-type magnetisation: the sites grouped by type, in
+// chunks of one type each, and a window of MCS whose chunk sums
+// (part [win][nchunk][3][Rp]) are kept until their records are written.
+struct TypeSums {
+    const int32_t *list;              // sites (internal order), type after type
+    const int32_t *chunk;             // [nchunk + 1] first entry of each chunk
+    double *part;
+    int32_t nchunk, win;
+    int32_t first[kMaxTypes + 1];     // first chunk of each type
+};
+
 // One colour phase: its sites [cb, ce) and its tiles, tile0 .. tile0 + nt - 1
 // of all colours' tiles.
 struct RepPhase {
@@ -210,10 +221,14 @@ hipError_t launch_rep_sigma(hipStream_t st, const RepLaneArgs &a, int ntiles, in
 hipError_t launch_rep_reduce(hipStream_t st, const RepLaneArgs &a, int ntiles, int t_first,
                              int count, int advance, const RunArgs &ra);
 // Optional outputs (output_kernels.hip).
-int type_part_blocks(bool replica_layout, int max_n);
+int type_part_blocks(int max_n);   // site and block layouts
 hipError_t launch_type_mag_site(hipStream_t st, bool f64, const RepDesc *reps, int R, int max_n,
                                 int t_off, const RunArgs &ra);
-hipError_t launch_type_mag_rep(hipStream_t st, const RepLaneArgs &a, int t_off, const RunArgs &ra);
+// Replica layout: the sums of MCS t_off into their slot of the window, and the
+// records of MCS t_first .. t_first + count - 1 (count <= ts.win) from it.
+hipError_t launch_type_sums_rep(hipStream_t st, const RepLaneArgs &a, const TypeSums &ts, int t_off);
+hipError_t launch_type_final_rep(hipStream_t st, const RepLaneArgs &a, const TypeSums &ts, int t_first,
+                                 int count, const RunArgs &ra);
 hipError_t launch_snapshot_site(hipStream_t st, bool f64, const RepDesc *reps, int R, int max_n,
                                 int t_off, bool check, const RunArgs &ra);
 hipError_t launch_snapshot_rep(hipStream_t st, const RepLaneArgs &a, int t_off, bool check,

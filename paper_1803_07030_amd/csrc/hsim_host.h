@@ -166,7 +166,9 @@ struct hsim_batch_s {
     // optional outputs (caller-owned device buffers) and their scratch
     double *type_mag = nullptr, *snapshots = nullptr;
     int32_t tm_types = 0;
-    hsim::DevBuf d_tm_part;
+    hsim::DevBuf d_tm_part, d_tm_sites;
+    hsim::TypeSums tsums{};         // replica layout
+    void build_type_sums();         // its tables and scratch, from the plan's types
     void reset_sigma();             // every replica's adaptive width to sigma0
     int32_t rec_win = 2;              // replica layout: MCS per record window
     // replica layout: bytes of the record window, its chunk sums and totals,

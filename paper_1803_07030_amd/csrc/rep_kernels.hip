@@ -652,30 +652,56 @@ __global__ __launch_bounds__(kRepThreads) void k_rep_phase(RepPhase ph, int t_of
 }
 
 // Adaptive widths after MCS t_off of the sequence: the accepted adaptive
-// moves of every replica (record field 6 of all tiles of the MCS) are summed
-// in kChunks fixed chunks of tiles, one per block, each in tile order; the
-// last block to finish adds the chunks in order and steers every width.
-__global__ __launch_bounds__(256) void k_rep_sigma(RepLaneArgs a, int ntiles, int t_off, RunArgs ra)
+// moves of every replica (record field 6 of all tiles of the MCS; whole
+// numbers, so any grouping gives the same sums) are summed by gridDim.x
+// blocks of 16 waves, a wave's lanes over replicas and the waves over tiles;
+// the last block to finish adds the blocks' sums and steers every width.
+// One block up to kSigmaOneBlock tiles, which needs no counter and no fence:
+// 261 tiles x 32 replicas took 9.9 us in 64 blocks whose lanes walked their
+// tiles one by one, 5.0 us in one block.
+constexpr int kSigmaWaves = 16, kSigmaOneBlock = 512, kSigmaBlocks = 16;
+static_assert(kSigmaBlocks <= kChunks, "the partial sums have kChunks rows");
+
+__global__ __launch_bounds__(kSigmaWaves * 64) void k_rep_sigma(RepLaneArgs a, int ntiles, int t_off, RunArgs ra)
 {
+    __shared__ double lds[kSigmaWaves][64];
     __shared__ int last;
-    const double *rec = rep_slot(ra, a, ntiles, t_off % ra.rec_win);
-    const int k = blockIdx.x;
-    const int tb = (int)((int64_t)ntiles * k / kChunks), te = (int)((int64_t)ntiles * (k + 1) / kChunks);
-    for (int r = threadIdx.x; r < a.R; r += blockDim.x) {
+    const double *rec = rep_slot(ra, a, ntiles, t_off % ra.rec_win) + (size_t)6 * a.Rp;
+    const size_t stride = (size_t)kRecFields * a.Rp;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int nb = gridDim.x, k = blockIdx.x;
+    const int tb = (int)((int64_t)ntiles * k / nb), te = (int)((int64_t)ntiles * (k + 1) / nb);
+    auto adapt = [&](int r, double n) {
+        ra.sigma[r] = adapted_sigma(ra.sigma[r], n, ra.n_ad[r], ra.pol.sigma_min, ra.pol.sigma_max);
+    };
+    for (int r0 = 0; r0 < a.R; r0 += 64) {
+        const int r = r0 + lane;
         double v = 0.0;
-        for (int tg = tb; tg < te; ++tg) v += rec[((size_t)tg * kRecFields + 6) * a.Rp + r];
-        ra.sig_part[(size_t)k * a.Rp + r] = v;
+        if (r < a.R)
+#pragma unroll 8
+            for (int tg = tb + w; tg < te; tg += kSigmaWaves) v += rec[(size_t)tg * stride + r];
+        lds[w][lane] = v;
+        __syncthreads();
+        if (w == 0 && r < a.R) {
+            double n = 0.0;
+#pragma unroll
+            for (int q = 0; q < kSigmaWaves; ++q) n += lds[q][lane];
+            if (nb == 1) adapt(r, n);
+            else ra.sig_part[(size_t)k * a.Rp + r] = n;
+        }
+        __syncthreads();
     }
+    if (nb == 1) return;
     __threadfence();
     __syncthreads();
-    if (threadIdx.x == 0) last = (atomicAdd(&ra.ctl->pad[2], 1u) == kChunks - 1);
+    if (threadIdx.x == 0) last = (atomicAdd(&ra.ctl->pad[2], 1u) == (uint32_t)nb - 1);
     __syncthreads();
     if (!last) return;
     __threadfence();
     for (int r = threadIdx.x; r < a.R; r += blockDim.x) {
         double n = 0.0;
-        for (int q = 0; q < kChunks; ++q) n += ra.sig_part[(size_t)q * a.Rp + r];
-        ra.sigma[r] = adapted_sigma(ra.sigma[r], n, ra.n_ad[r], ra.pol.sigma_min, ra.pol.sigma_max);
+        for (int q = 0; q < nb; ++q) n += ra.sig_part[(size_t)q * a.Rp + r];
+        adapt(r, n);
     }
     if (threadIdx.x == 0) ra.ctl->pad[2] = 0;
 }
@@ -1097,7 +1123,8 @@ hipError_t launch_rep_phase(hipStream_t st, int kmode, int fmode, int colour, in
 hipError_t launch_rep_sigma(hipStream_t st, const RepLaneArgs &a, int ntiles, int t_off,
                             const RunArgs &ra)
 {
-    hipLaunchKernelGGL(k_rep_sigma, dim3(kChunks), dim3(256), 0, st, a, ntiles, t_off, ra);
+    hipLaunchKernelGGL(k_rep_sigma, dim3(ntiles <= kSigmaOneBlock ? 1 : kSigmaBlocks), dim3(kSigmaWaves * 64), 0,
+                       st, a, ntiles, t_off, ra);
     return hipGetLastError();
 }
 
