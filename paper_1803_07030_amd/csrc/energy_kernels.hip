@@ -8,7 +8,7 @@
 // bond order; anisotropy axes and field directions [3][n].
 //
 // A sparse gather: every site reads its neighbours in each configuration.
-// Work items are (group of kEG configurations, tile of kEBlock sites); items
+// Work items are (group of up to kEG configurations, tile of kEBlock sites); items
 // are dealt to the 8 XCDs in contiguous ranges (group-major), so the tiles
 // holding a tile's neighbours are processed by the same XCD at about the same
 // time and the neighbour reads hit its L2.  Rows of at most 8 entries are
@@ -37,7 +37,7 @@ namespace hsim {
 namespace {
 
 constexpr int kEBlock = 256;   // sites per tile, one per thread
-constexpr int kEG = 32;        // configurations per work item
+constexpr int kEG = 32;        // configurations per work item, at most (EnergyArgs::eg)
 constexpr int kEU = 2;         // configurations whose loads are in flight together
 
 __device__ __forceinline__ double wsum(double v)
@@ -211,8 +211,8 @@ __device__ __forceinline__ void energy_ell(const EnergyArgs &a, int ntile, int i
         loc[q] = STAGE && d >= 0 && d < kEBlock ? (int)d : -1;
     }
     const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-    const int b0 = grp * kEG;
-    const int nc = min(kEG, a.batch - b0);
+    const int b0 = grp * a.eg;
+    const int nc = min(a.eg, a.batch - b0);
     const bool params = BWD && (partK || partJ);
     // dE/dk and dE/dJ of the group, summed over its configurations in the
     // spins' precision (at most kEG terms), then handed on in double
@@ -268,8 +268,7 @@ __device__ __forceinline__ void energy_ell(const EnergyArgs &a, int ntile, int i
         T go[BWD ? kEU : 1][3];
 #pragma unroll
         for (int u = 0; u < kEU; ++u) {
-            const int c = c0 + u, b = b0 + c;
-            const bool ok = live && c < nc;
+            const bool ok = live && c0 + u < nc;
             // exchange field, entries in CSR order (padding adds 0 * S_i)
             T thx = T(0), thy = T(0), thz = T(0);
 #pragma unroll
@@ -418,7 +417,7 @@ __global__ __launch_bounds__(kEBlock) void k_energy_csr(EnergyArgs a, const doub
     const bool live = i < a.n;
     const SiteTables<T> st(a, live ? i : 0);
     const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-    const int b0 = (int)blockIdx.y * kEG;
+    const int b0 = (int)blockIdx.y * a.eg;
     // backward, parameter gradients of the chunk: dE/dk_i and dE/dJ of the
     // bonds whose lower end is i (rows up to kMaxNb entries here; longer rows
     // below), summed over the chunk's configurations in order
@@ -426,7 +425,7 @@ __global__ __launch_bounds__(kEBlock) void k_energy_csr(EnergyArgs a, const doub
     double gk = 0.0, gj[kMaxNb];
 #pragma unroll
     for (int q = 0; q < kMaxNb; ++q) gj[q] = 0.0;
-    for (int c = 0; c < kEG; ++c) {
+    for (int c = 0; c < a.eg; ++c) {
         const int b = b0 + c;
         if (b >= a.batch) break;   // uniform over the block
         double e = 0.0, zn = 0.0;
@@ -485,7 +484,7 @@ __global__ __launch_bounds__(kEBlock) void k_energy_csr(EnergyArgs a, const doub
         }
     }
     __syncthreads();
-    const int nc = min(kEG, a.batch - b0);
+    const int nc = min(a.eg, a.batch - b0);
     if ((int)threadIdx.x < nc) {
         const int c = threadIdx.x, b = b0 + c;
         const size_t t = (size_t)b * gridDim.x + blockIdx.x;
@@ -506,7 +505,7 @@ __global__ __launch_bounds__(kEBlock) void k_energy_csr(EnergyArgs a, const doub
         for (int q = 0; q < kMaxNb; ++q)
             if (q < st.deg && st.col[q] > i) partJ[ch * a.nb + a.bond[st.rb + q]] = gj[q];
     } else {
-        const int b1 = min(a.batch, b0 + kEG);
+        const int b1 = min(a.batch, b0 + a.eg);
         for (int64_t p = st.rb; p < st.rb + st.deg; ++p) {
             const int64_t j = a.ci[p];
             if (j <= i) continue;
@@ -524,15 +523,20 @@ __global__ __launch_bounds__(kEBlock) void k_energy_csr(EnergyArgs a, const doub
 
 // Per-configuration sums of tile partials: one wave per configuration,
 // lanes over tiles lane-strided in order, then a butterfly.
-__global__ __launch_bounds__(256) void k_energy_tiles(int cnt, int ntile, const double *part,
-                                                      double *out)
+__device__ __forceinline__ void tile_sum(int block, int cnt, int ntile, const double *part, double *out)
 {
-    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), ln = threadIdx.x & 63;
+    const int b = block * 4 + (threadIdx.x >> 6), ln = threadIdx.x & 63;
     if (b >= cnt) return;
     double v = 0.0;
     for (int t = ln; t < ntile; t += 64) v += part[(size_t)b * ntile + t];
     v = wsum(v);
     if (ln == 0) out[b] = v;
+}
+
+__global__ __launch_bounds__(256) void k_energy_tiles(int cnt, int ntile, const double *part,
+                                                      double *out)
+{
+    tile_sum(blockIdx.x, cnt, ntile, part, out);
 }
 
 // Sum of column t of part [ngroups][stride] in group order; the loads of
@@ -552,15 +556,44 @@ __device__ __forceinline__ double group_sum(const double *part, int ngroups, int
     return v;
 }
 
-// dE/dk and dE/dJ of a pass: the groups' partials summed in order, added to
-// the sums of the earlier passes (first: start them); the last pass writes
-// the outputs in the inputs' precision.
+// What is left of a backward pass after the site kernel, in one launch (a
+// launch costs a small call more than its work).  The first pblocks blocks:
+// dE/dk and dE/dJ, the groups' partials summed in order, added to the sums of
+// the earlier passes (first: start them); the last pass writes the outputs in
+// the inputs' precision.  The blocks after them, for dE/dB: up to kGBDirect
+// records, one block sums them all (thread t takes t, t + 256, ...; then the
+// block sum) and adds the earlier passes'; of more records, each wave sums a
+// configuration's tiles and k_energy_gB the configurations.
+constexpr int64_t kGBDirect = 16384;   // 64 records per thread
+
+__device__ __forceinline__ void gB_sum(int64_t cnt, const double *p, double *accB, int first, int last,
+                                       double *gB)
+{
+    __shared__ double red[4];
+    double v = 0.0;
+#pragma unroll 4
+    for (int64_t t = threadIdx.x; t < cnt; t += blockDim.x) v += p[t];
+    v = bsum(v, red);
+    if (threadIdx.x == 0) {
+        if (!first) v = accB[0] + v;
+        if (last) gB[0] = v;
+        else accB[0] = v;
+    }
+}
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_energy_params(int64_t n, int64_t nb, int ngroups,
+__global__ __launch_bounds__(256) void k_energy_finish(int64_t n, int64_t nb, int ngroups,
                                                        const double *partK, const double *partJ,
                                                        double *accK, double *accJ, int first,
-                                                       int last, T *gk, T *gJ)
+                                                       int last, T *gk, T *gJ, int pblocks, int cnt,
+                                                       int ntile, const double *partB, double *pB,
+                                                       double *accB, double *gB)
 {
+    if ((int)blockIdx.x >= pblocks) {
+        if ((int64_t)cnt * ntile <= kGBDirect) gB_sum((int64_t)cnt * ntile, partB, accB, first, last, gB);
+        else tile_sum((int)blockIdx.x - pblocks, cnt, ntile, partB, pB);
+        return;
+    }
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gJ && t < nb) {
         double v = group_sum(partJ, ngroups, nb, t);
@@ -576,20 +609,11 @@ __global__ __launch_bounds__(256) void k_energy_params(int64_t n, int64_t nb, in
     }
 }
 
-// dE/dB of a pass: its configurations' sums in a fixed order (thread t takes
-// t, t + 256, ...; then the block sum), added to the earlier passes'.
+// dE/dB of a pass from its configurations' sums.
 __global__ __launch_bounds__(256) void k_energy_gB(int cnt, const double *pB, double *accB,
                                                    int first, int last, double *gB)
 {
-    __shared__ double red[4];
-    double v = 0.0;
-    for (int t = threadIdx.x; t < cnt; t += blockDim.x) v += pB[t];
-    v = bsum(v, red);
-    if (threadIdx.x == 0) {
-        if (!first) v = accB[0] + v;
-        if (last) gB[0] = v;
-        else accB[0] = v;
-    }
+    gB_sum(cnt, pB, accB, first, last, gB);
 }
 
 EnergyLayout energy_layout(int64_t n, int64_t nb, int ell_w, int64_t cap_doubles, bool forward_only,
@@ -637,7 +661,7 @@ hipError_t launch_site_kernel(hipStream_t st, const EnergyArgs &a, const EnergyL
                               const double *gE, T *gS, double *partE, double *partB,
                               double *partK, double *partJ)
 {
-    const int ngroups = (a.batch + kEG - 1) / kEG;
+    const int ngroups = (a.batch + a.eg - 1) / a.eg;
     if (!BWD && a.hcol && (L.ell_w == 6 || L.ell_w == 8)) {
         // the forward needs every bond once: half rows of width ell_w / 2
         const int items = ngroups * L.ntile;
@@ -669,14 +693,33 @@ hipError_t launch_site_kernel(hipStream_t st, const EnergyArgs &a, const EnergyL
     return hipGetLastError();
 }
 
+// Configurations per work item of a pass of cnt: the largest power of two, 32
+// to kEU, that gives kEnergyItems items (4 per CU), and never more groups
+// than the scratch holds (L.groups).  A call of a few groups of 32 leaves most
+// of the chip idle while each block walks its group two configurations at a
+// time.  Forward and backward, us, groups of 32 | by this rule: 75
+// configurations of a film of 16,700 sites 75.9 | 48.6 (with the weights and
+// the conversion of the states); SC 16^3 x 64 50.0 | 29.2; SC 20^3 x 300 in
+// double precision 89.1 | 66.4 (72.3 with 512 items); from 1024 items of 32
+// on, as SC 32^3 x 1024, the rule changes nothing.
+constexpr int64_t kEnergyItems = 1024;
+int group_size(const EnergyLayout &L, int cnt)
+{
+    int g = kEG;
+    while (g > kEU && (int64_t)((cnt + g - 1) / g) * L.ntile < kEnergyItems && (cnt + g / 2 - 1) / (g / 2) <= L.groups)
+        g /= 2;
+    return g;
+}
+
 // The pass [b0, b0 + cnt) of the batch: the arguments with the spins (and
 // their gradients) moved to the pass's first configuration.
-EnergyArgs pass_args(const EnergyArgs &a, bool f64, int b0, int cnt)
+EnergyArgs pass_args(const EnergyArgs &a, const EnergyLayout &L, bool f64, int b0, int cnt)
 {
     EnergyArgs p = a;
     const size_t es = f64 ? 8 : 4;
     p.S = (const char *)a.S + (size_t)b0 * 3 * a.n * es;
     p.batch = cnt;
+    p.eg = group_size(L, cnt);
     return p;
 }
 
@@ -688,7 +731,7 @@ hipError_t launch_energy_forward(hipStream_t st, bool f64, const EnergyArgs &a,
     if (L.pass_cfg < 1) return hipErrorInvalidValue;
     for (int b0 = 0; b0 < a.batch; b0 += L.pass_cfg) {
         const int cnt = std::min(L.pass_cfg, a.batch - b0);
-        const EnergyArgs p = pass_args(a, f64, b0, cnt);
+        const EnergyArgs p = pass_args(a, L, f64, b0, cnt);
         double *partE = scratch + L.off_partE;
         hipError_t e = f64 ? launch_site_kernel<double, false>(st, p, L, nullptr, nullptr, partE, nullptr, nullptr, nullptr)
                            : launch_site_kernel<float, false>(st, p, L, nullptr, nullptr, partE, nullptr, nullptr, nullptr);
@@ -714,34 +757,28 @@ hipError_t launch_energy_backward(hipStream_t st, bool f64, const EnergyArgs &a,
     for (int b0 = 0; b0 < a.batch; b0 += L.pass_cfg) {
         const int cnt = std::min(L.pass_cfg, a.batch - b0);
         const int first = b0 == 0, last = b0 + cnt >= a.batch;
-        const EnergyArgs p = pass_args(a, f64, b0, cnt);
+        const EnergyArgs p = pass_args(a, L, f64, b0, cnt);
         void *gSp = gS ? (char *)gS + (size_t)b0 * 3 * a.n * es : nullptr;
         double *pk = gk ? partK : nullptr, *pj = gJ ? partJ : nullptr;
         hipError_t e = f64 ? launch_site_kernel<double, true>(st, p, L, gE + b0, (double *)gSp, nullptr, partB, pk, pj)
                            : launch_site_kernel<float, true>(st, p, L, gE + b0, (float *)gSp, nullptr, partB, pk, pj);
         if (e != hipSuccess) return e;
-        if (gJ || gk) {
-            const int ng = (cnt + kEG - 1) / kEG;
-            const dim3 g3((unsigned)((m + 255) / 256));
-            if (f64)
-                hipLaunchKernelGGL((k_energy_params<double>), g3, dim3(256), 0, st, a.n, a.nb, ng,
-                                   (const double *)partK, (const double *)partJ, accK, accJ, first,
-                                   last, (double *)gk, (double *)gJ);
-            else
-                hipLaunchKernelGGL((k_energy_params<float>), g3, dim3(256), 0, st, a.n, a.nb, ng,
-                                   (const double *)partK, (const double *)partJ, accK, accJ, first,
-                                   last, (float *)gk, (float *)gJ);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        if (gB) {
-            hipLaunchKernelGGL(k_energy_tiles, dim3((unsigned)((cnt + 3) / 4)), dim3(256), 0, st, cnt,
-                               L.ntile, (const double *)partB, pB);
-            hipLaunchKernelGGL(k_energy_gB, dim3(1), dim3(256), 0, st, cnt, (const double *)pB, accB,
-                               first, last, gB);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
+        const int ng = (cnt + p.eg - 1) / p.eg;
+        const int pblocks = gJ || gk ? (int)((m + 255) / 256) : 0;
+        const bool direct = (int64_t)cnt * L.ntile <= kGBDirect;
+        const int bblocks = !gB ? 0 : direct ? 1 : (cnt + 3) / 4;
+        if (pblocks + bblocks == 0) continue;
+        auto finish = [&](auto kernel, auto *gk_, auto *gJ_) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(pblocks + bblocks)), dim3(256), 0, st, a.n, a.nb, ng,
+                               (const double *)partK, (const double *)partJ, accK, accJ, first, last, gk_, gJ_,
+                               pblocks, cnt, L.ntile, (const double *)partB, pB, accB, gB);
+        };
+        if (f64) finish(k_energy_finish<double>, (double *)gk, (double *)gJ);
+        else finish(k_energy_finish<float>, (float *)gk, (float *)gJ);
+        if (gB && !direct)
+            hipLaunchKernelGGL(k_energy_gB, dim3(1), dim3(256), 0, st, cnt, (const double *)pB, accB, first, last, gB);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -250,6 +250,7 @@ struct EnergyArgs {
     const int32_t *hbond;   // [ell_w/2][n] their bond ids (-1 past the row)
     int64_t n, nnz, nb;
     int batch;
+    int eg;                 // configurations per work item
     const void *S, *Jb, *k, *ax, *nd;
     const void *kc;         // NULL, or [n] cubic constants of the plan (user order)
     double B;

@@ -50,10 +50,11 @@ class HeisenbergEnergy(torch.autograd.Function):
         J_bond, k, axis = J_bond.contiguous(), k.contiguous(), axis.contiguous()
         fd = None if field_dir is None else field_dir.contiguous()
         batch = spins.shape[0]
+        Bv = float(B)                    # of a device tensor: waits for it, so once
         E = torch.empty(batch, dtype=torch.float64, device=spins.device)
-        hsim.hsim_energy_forward(plan.handle, batch, prec, spins, J_bond, k, axis, float(B), fd, E)
+        hsim.hsim_energy_forward(plan.handle, batch, prec, spins, J_bond, k, axis, Bv, fd, E)
         ctx.save_for_backward(spins, J_bond, k, axis)
-        ctx.fd, ctx.plan, ctx.prec, ctx.B = fd, plan, prec, float(B)
+        ctx.fd, ctx.plan, ctx.prec, ctx.B = fd, plan, prec, Bv
         return E
 
     @staticmethod
