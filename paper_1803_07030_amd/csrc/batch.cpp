@@ -1056,6 +1056,22 @@ bool run_persistent(hsim_batch b, const hsim::RunArgs &ra, hipStream_t st, uint3
     return true;
 }
 
+// Whether a block-layout run can take the pipelined kernel: what it holds in
+// registers and LDS covers double precision, spins in LDS, padded rows, one
+// or two classes of at most 256 sites (block_threads), the random move, no
+// cubic terms or spin lengths, no per-type output.
+bool block_pipe_ok(hsim_batch b)
+{
+    if (!b->f64 || !b->lds || b->block_threads > 256 || b->ellw == 0 || b->pol.n_types > 0 || b->type_mag) return false;
+    int64_t max_pad = 0;
+    for (auto p : b->plans) {
+        if (p->n > 0 && (p->ncol < 1 || p->ncol > 2)) return false;
+        if (!p->kcd.empty() || !p->mud.empty()) return false;
+        max_pad = std::max(max_pad, pad64(p->n));
+    }
+    return (int64_t)hsim::block_pipe_lds(b->block_threads, max_pad) <= device_lds_limit();
+}
+
 }  // namespace
 
 void batch_run_impl(hsim_batch b, int32_t first_step, int32_t n_steps, const double *T,
@@ -1144,6 +1160,14 @@ void batch_run_impl(hsim_batch b, int32_t first_step, int32_t n_steps, const dou
     const hsim::RunArgs ra = b->run_args(g0, n_mcs, P, want_trace ? trace : nullptr);
     hip_check(hsim::launch_ctl_set(st, ra.ctl, g0), "control launch");
 
+    if (b->layout == HSIM_LAYOUT_BLOCK && block_pipe_ok(b)) {
+        int64_t max_pad = 0;
+        for (auto p : b->plans) max_pad = std::max(max_pad, pad64(p->n));
+        hip_check(hsim::launch_block_pipe(st, b->kmode, b->fmode, want_trace, b->ellw, b->block_threads, max_pad,
+                                          (const hsim::RepDesc *)b->d_reps.p, ra),
+                  "block sweep launch");
+        return;
+    }
     if (b->layout == HSIM_LAYOUT_BLOCK) {
         hip_check(hsim::launch_block_sweep(st, b->f64, b->kmode, b->fmode, want_trace, b->ellw, b->lds,
                                            b->block_threads, b->lds_bytes,

@@ -207,6 +207,12 @@ hipError_t launch_block_sweep(hipStream_t st, bool f64, int kmode, int fmode, bo
                               int ellw, bool lds, int threads, size_t lds_bytes, const RepDesc *reps,
                               const RunArgs &ra);
 int block_sweep_max_lds(bool f64);
+// Pipelined double-precision block kernel (padded rows, at most two classes of
+// at most `workers` sites, workers a multiple of 64 up to 256; random moves,
+// no cubic terms, spin lengths or per-type output) and its LDS.
+size_t block_pipe_lds(int workers, int64_t max_pad);
+hipError_t launch_block_pipe(hipStream_t st, int kmode, int fmode, bool trace, int ellw, int workers,
+                             int64_t max_pad, const RepDesc *reps, const RunArgs &ra);
 
 hipError_t launch_rep_phase(hipStream_t st, int kmode, int fmode, int colour, int t_off,
                             const RepLaneArgs &a, int ntiles, const RunArgs &ra);

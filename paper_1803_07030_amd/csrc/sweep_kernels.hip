@@ -15,6 +15,7 @@
 // the per-MCS reduction adds tile records in table order.
 #include "hsim_dev.h"
 #include "update.h"
+#include "wave.h"
 
 namespace hsim {
 
@@ -742,6 +743,240 @@ __global__ __launch_bounds__(NT) void k_block_sweep(const RepDesc *__restrict__ 
     }
 }
 
+// ------------------------------------------- block layout, pipelined (double)
+// A double-precision replica with one or two colour classes of at most 256
+// sites (the validation runs): one workgroup, spins in LDS, and the work of an
+// MCS dealt to waves by kind, so that what does not depend on the spins is off
+// the chain of the colour phases:
+//   worker waves, a thread per site of each class: field, energy change,
+//     acceptance; a site's row and parameters stay in registers for the run;
+//   drawing waves, twice as many: the acceptance words and trial points of
+//     the next MCS (they depend on the counters only), into LDS;
+//   one of them also adds the workers' sums of the last MCS and writes its
+//     history.
+// Two barriers per MCS (three when the energy is recomputed) hand everything
+// over; draws and sums have two buffers, by MCS parity.  The operations of an
+// update are update64's in its order, so the trajectory is unchanged bit for
+// bit.  One workgroup is bound by latency: SC 8^3 took 6.9 us per MCS with
+// every thread drawing, updating and reducing in turn.
+constexpr int kPipeMax = 256;                    // workers at most
+constexpr int kPipeRed = 6;                      // sums per worker: dE, M, accepted, energy
+
+size_t block_pipe_lds(int workers, int64_t max_pad)
+{
+    return (size_t)(3 * max_pad + (2 * 2 * 4 + 2 * kPipeRed) * (int64_t)workers) * sizeof(double);
+}
+
+// Acceptance uniform and trial point of one site: update64's draw and
+// sphere64's map, two attempts at a time (independent chains).
+__device__ __forceinline__ void draw_site64(uint64_t seed, uint32_t site, uint32_t g, uint32_t rep, double &u,
+                                            double &x, double &y, double &z)
+{
+    const uint4 w0 = draw(seed, site, g, rep, 0);
+    double v1 = 0.0, v2 = 0.0, s = 2.0;
+    for (uint32_t t = 1; t <= 32 && !(s < 1.0); t += 2) {
+        const uint4 a = draw(seed, site, g, rep, t), b = draw(seed, site, g, rep, t + 1);
+        const double a1 = 2.0 * u53(a.x, a.y) - 1.0, a2 = 2.0 * u53(a.z, a.w) - 1.0;
+        const double b1 = 2.0 * u53(b.x, b.y) - 1.0, b2 = 2.0 * u53(b.z, b.w) - 1.0;
+        const double sa = a1 * a1 + a2 * a2, sb = b1 * b1 + b2 * b2;
+        const bool first = sa < 1.0;
+        v1 = first ? a1 : b1;
+        v2 = first ? a2 : b2;
+        s = first ? sa : sb;
+    }
+    u = u53(w0.x, w0.y);
+    const double f = 2.0 * sqrt(1.0 - (s < 1.0 ? s : 0.0));
+    x = s < 1.0 ? v1 * f : 0.0;                  // no point in 32 attempts: +z
+    y = s < 1.0 ? v2 * f : 0.0;
+    z = s < 1.0 ? 1.0 - 2.0 * s : 1.0;
+}
+
+template <int KM, int FM, bool TRACE, int MAXD>
+__global__ __launch_bounds__(3 * kPipeMax) void k_block_pipe(const RepDesc *__restrict__ reps, RunArgs ra,
+                                                             int max_pad)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int rep = blockIdx.x;
+    const RepDesc &rd = reps[rep];
+    const int np = rd.n_pad, n = rd.n, nw = (int)blockDim.x / 3;
+    double *G = (double *)rd.spins, *S = (double *)smem;
+    double *D = S + 3 * (size_t)max_pad;         // draws [parity][class][u, x, y, z][nw]
+    double *R = D + 2 * 2 * 4 * nw;              // sums [parity][kPipeRed][nw]
+    for (int i = threadIdx.x; i < 3 * n; i += blockDim.x) {
+        const int c = i / n, k = c * np + (i - c * n);
+        S[k] = G[k];
+    }
+    const bool worker = (int)threadIdx.x < nw;
+    const int h = (int)threadIdx.x - nw, ncol = rd.ncol;
+    // drawing thread h: class h / nw, its site h % nw
+    const int dc = h >= nw ? 1 : 0, dj = h - dc * nw;
+    const bool dlive = !worker && dc < ncol && dj < rd.cls_off[dc + 1] - rd.cls_off[dc];
+    const uint32_t dorig = dlive ? rd.orig[rd.cls_off[dc] + dj] : 0u;
+    auto produce = [&](uint32_t g, int par) {
+        if (!dlive) return;
+        double u, x, y, z;
+        draw_site64(ra.seed, dorig, g, rd.rep_id, u, x, y, z);
+        double *d = D + (size_t)(par * 2 + dc) * 4 * nw + dj;
+        d[0] = u;
+        d[nw] = x;
+        d[2 * nw] = y;
+        d[3 * nw] = z;
+    };
+    const bool reducer = !worker && h >= 2 * nw - 64;
+    const int lane = threadIdx.x & 63;
+    double E = 0.0;
+    // sums and history record of MCS t of the run
+    auto record = [&](int t) {
+        const uint32_t g = ra.g0 + (uint32_t)t, s_abs = g / (uint32_t)ra.M, m = g % (uint32_t)ra.M;
+        const double *r = R + (size_t)(t & 1) * kPipeRed * nw + lane;
+        double v[kPipeRed];
+#pragma unroll
+        for (int q = 0; q < kPipeRed; ++q) {
+            v[q] = r[q * nw];
+            for (int w = 64; w < nw; w += 64) v[q] += r[q * nw + w];
+        }
+#pragma unroll
+        for (int q = 0; q < kPipeRed; ++q) v[q] = wave_all(v[q], OpAdd());
+        E = (recompute_due(m, ra.P) ? v[5] : E) + v[0];
+        if (lane < 5) {
+            double *hist = ra.history + (((size_t)rep * ra.S_hist + s_abs) * ra.M + m) * 5;
+            hist[lane] = lane == 0 ? E : lane == 1 ? v[1] : lane == 2 ? v[2] : lane == 3 ? v[3] : v[4];
+        }
+    };
+    // a worker's sites: row, parameters
+    int site[2] = {0, 0}, col[2][MAXD];
+    double J[2][MAXD];
+    bool live[2] = {false, false};
+    uint32_t orig[2] = {0u, 0u};
+    struct P7 {
+        double k, ex, ey, ez, nx, ny, nz;
+    } pr[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        live[c] = worker && c < ncol && rd.cls_off[c] + (int)threadIdx.x < rd.cls_off[c + 1];
+        const int i = live[c] ? rd.cls_off[c] + (int)threadIdx.x : 0;
+        site[c] = i;
+        if (worker) {
+            orig[c] = rd.orig[i];
+#pragma unroll
+            for (int sl = 0; sl < MAXD; ++sl) {
+                col[c][sl] = rd.ellT_col[sl * n + i];
+                J[c][sl] = ((const double *)rd.ellT_J)[sl * n + i];
+            }
+            const SiteParams<double, KM, FM> sp(rd, i);
+            pr[c] = P7{sp.k, sp.ex, sp.ey, sp.ez, sp.nx, sp.ny, sp.nz};
+        }
+    }
+    if (!worker) produce(ra.g0, 0);
+    __syncthreads();
+    double beta = 0.0, b = 0.0;
+    uint32_t s_abs = ra.g0 / (uint32_t)ra.M, m = ra.g0 % (uint32_t)ra.M;
+    for (int t = 0; t < ra.n_mcs_run; ++t) {
+        const uint32_t g = ra.g0 + (uint32_t)t;
+        const bool due = recompute_due(m, ra.P);
+        if (worker) {
+            if (t == 0 || m == 0) {
+                beta = ra.beta[(size_t)rep * ra.S_hist + s_abs];
+                b = ra.bfield[(size_t)rep * ra.S_hist + s_abs];
+            }
+            double acc[kPipeRed] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            // exchange field at a site, in row order (padding adds 0 * S_i)
+            auto field = [&](int c, double &hx, double &hy, double &hz) {
+                hx = 0.0;
+                hy = 0.0;
+                hz = 0.0;
+#pragma unroll
+                for (int sl = 0; sl < MAXD; ++sl) {
+                    const int j = col[c][sl];
+                    hx = hx + J[c][sl] * S[j];
+                    hy = hy + J[c][sl] * S[np + j];
+                    hz = hz + J[c][sl] * S[2 * np + j];
+                }
+            };
+            if (due) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    if (live[c]) {
+                        double hx, hy, hz;
+                        field(c, hx, hy, hz);
+                        const int i = site[c];
+                        const double sx = S[i], sy = S[np + i], sz = S[2 * np + i];
+                        const double an = sx * pr[c].ex + sy * pr[c].ey + sz * pr[c].ez;
+                        const double zn = sx * pr[c].nx + sy * pr[c].ny + sz * pr[c].nz;
+                        acc[5] += -0.5 * (sx * hx + sy * hy + sz * hz) - b * zn - pr[c].k * an * an;
+                    }
+                __syncthreads();   // every energy is read before the first update
+            }
+            auto update = [&](int c) {
+                if (!live[c]) return;
+                const double *d = D + (size_t)((t & 1) * 2 + c) * 4 * nw + threadIdx.x;
+                const double u = d[0], tx = d[nw], ty = d[2 * nw], tz = d[3 * nw];
+                const int i = site[c];
+                const double sx = S[i], sy = S[np + i], sz = S[2 * np + i];
+                double hx, hy, hz;
+                field(c, hx, hy, hz);
+                hx = hx + b * pr[c].nx;
+                hy = hy + b * pr[c].ny;
+                hz = hz + b * pr[c].nz;
+                const double dSx = tx - sx, dSy = ty - sy, dSz = tz - sz;
+                const double q = (dSx * hx + dSy * hy) + dSz * hz;
+                const double a1 = dot64(tx, ty, tz, pr[c].ex, pr[c].ey, pr[c].ez);
+                const double a0 = dot64(sx, sy, sz, pr[c].ex, pr[c].ey, pr[c].ez);
+                const double dE = -q - pr[c].k * (a1 * a1 - a0 * a0);
+                const bool ok = dE <= 0.0 || u < exp(-beta * dE);
+                if (dE != dE) atomicOr(&ra.ctl->status, 1u);
+                if (ok) {
+                    S[i] = tx;
+                    S[np + i] = ty;
+                    S[2 * np + i] = tz;
+                    if (TRACE)
+                        atomicOr(&ra.trace[((size_t)rep * ra.n_mcs_run + t) * ra.trace_words + (orig[c] >> 5)],
+                                 1u << (orig[c] & 31));
+                }
+                acc[0] += ok ? dE : 0.0;
+                acc[4] += ok ? 1.0 : 0.0;
+                acc[1] += ok ? tx : sx;
+                acc[2] += ok ? ty : sy;
+                acc[3] += ok ? tz : sz;
+            };
+            update(0);
+            __syncthreads();
+            if (ncol > 1) update(1);
+#pragma unroll
+            for (int q = 0; q < kPipeRed; ++q) R[((size_t)(t & 1) * kPipeRed + q) * nw + threadIdx.x] = acc[q];
+            if (ra.snapshots && m + 1 == (uint32_t)ra.M)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    if (live[c]) {
+                        const int i = site[c];
+                        double *o = ra.snapshots + (((size_t)rep * ra.S_hist + s_abs) * ra.snap_n + orig[c]) * 3;
+                        o[0] = S[i];
+                        o[1] = S[np + i];
+                        o[2] = S[2 * np + i];
+                    }
+        } else {
+            if (due) __syncthreads();
+            // the two classes' draws in the two halves of the MCS: fewer waves
+            // at a time beside the workers
+            if (reducer && t > 0) record(t - 1);
+            if (dc == 0 && t + 1 < ra.n_mcs_run) produce(g + 1, (t + 1) & 1);
+            __syncthreads();
+            if (dc == 1 && t + 1 < ra.n_mcs_run) produce(g + 1, (t + 1) & 1);
+        }
+        __syncthreads();
+        if (++m == (uint32_t)ra.M) {
+            m = 0;
+            ++s_abs;
+        }
+    }
+    if (reducer && ra.n_mcs_run > 0) record(ra.n_mcs_run - 1);
+    if (reducer && lane == 0) ra.ecarry[rep] = E;
+    for (int i = threadIdx.x; i < 3 * n; i += blockDim.x) {
+        const int c = i / n, k = c * np + (i - c * n);
+        G[k] = S[k];
+    }
+}
+
 int block_sweep_max_lds(bool)
 {
     int dev = 0, v = 0;
@@ -749,6 +984,23 @@ int block_sweep_max_lds(bool)
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return 0;
     return v - 1024;   // static reduction scratch
+}
+
+hipError_t launch_block_pipe(hipStream_t st, int kmode, int fmode, bool trace, int ellw, int workers,
+                             int64_t max_pad, const RepDesc *reps, const RunArgs &ra)
+{
+    if (workers > kPipeMax || workers % 64 != 0 || (ellw != 6 && ellw != 8)) return hipErrorInvalidValue;
+    const size_t sh = block_pipe_lds(workers, max_pad);
+    HSIM_DISPATCH_KF(kmode, fmode, HSIM_DISPATCH_W(ellw, {
+        if constexpr (MAXD > 0) {
+            auto kfn = trace ? k_block_pipe<KM, FM, true, MAXD> : k_block_pipe<KM, FM, false, MAXD>;
+            if (sh > 65536)
+                (void)hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+            hipLaunchKernelGGL(kfn, dim3((unsigned)ra.R), dim3((unsigned)(3 * workers)), sh, st, reps, ra,
+                               (int)max_pad);
+        }
+    }));
+    return hipGetLastError();
 }
 
 hipError_t launch_block_sweep(hipStream_t st, bool f64, int kmode, int fmode, bool trace,
