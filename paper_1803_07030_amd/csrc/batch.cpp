@@ -508,6 +508,20 @@ void hsim_batch_s::upload_tables()
         if (layout == HSIM_LAYOUT_SITE) {
             d_tiles.upload(tiles);
             d_rep_tiles.upload(rep_tiles);
+            if (ellw > 0) {
+                std::vector<hsim::SiteDesc> sd(R);
+                for (int r = 0; r < R; ++r) {
+                    const hsim::RepDesc &d = reps[r];
+                    sd[r] = hsim::SiteDesc{d.ellT_col, d.ellT_J, d.spins, d.orig, d.k, d.ax, d.nd, d.k0,
+                                           {d.e0[0], d.e0[1], d.e0[2]}, {d.n0[0], d.n0[1], d.n0[2]}, d.n, d.n_pad,
+                                           d.rep_id, r};
+                }
+                std::vector<hsim::TileDesc> td(tiles.size());
+                for (size_t t = 0; t < tiles.size(); ++t)
+                    td[t] = hsim::TileDesc{sd[tiles[t].rep], tiles[t].begin, tiles[t].end, tiles[t].nsl, 0};
+                d_site_desc.upload(sd);
+                d_site_tiles.upload(td);
+            }
             for (int g = 0; g < ngroups; ++g) d_grp_reps[g].upload(grp_reps[g]);
         }
     }
@@ -822,6 +836,16 @@ void enqueue_outputs(hsim_batch b, const hsim::RunArgs &ra, int t, const StepEnd
     }
 }
 
+// Whether the site layout's launches can be those of the plain model: padded
+// rows, the random move everywhere, no cubic terms or spin lengths.
+bool site_plain(hsim_batch b)
+{
+    if (b->ellw == 0 || b->pol.n_types > 0) return false;
+    for (auto p : b->plans)
+        if (!p->kcd.empty() || !p->mud.empty()) return false;
+    return true;
+}
+
 // Site layout, one group's MCS t of a sequence: the energy recompute when
 // due, the colour phases below c_tail, the finish launch (trailing classes
 // and history) of the group's replicas.
@@ -837,17 +861,31 @@ void enqueue_site_mcs(hsim_batch b, const hsim::RunArgs &ra, int g, int t, F efu
                                           t, ra),
                   "efull launch");
     const bool timed = b->time_every > 0 && t % b->time_every == 0;
+    const bool plain = site_plain(b);
+    const auto *rlist = b->ngroups > 1 ? (const int32_t *)b->d_grp_reps[g].p : nullptr;
     for (int c = 0; c < b->c_tail; ++c) {
         PhaseTimer pt(b, st, timed && to[c + 1] > to[c], c, b->gunits[g][c]);
-        hip_check(hsim::launch_site_phase(st, b->f64, b->kmode, b->fmode, ra.trace != nullptr, b->ellw, reps,
+        if (plain)
+            hip_check(hsim::launch_site_plain(st, b->f64, b->kmode, b->fmode, ra.trace != nullptr, b->ellw,
+                                              (const hsim::TileDesc *)b->d_site_tiles.p, to[c], to[c + 1] - to[c],
+                                              t, ra),
+                      "phase launch");
+        else
+            hip_check(hsim::launch_site_phase(st, b->f64, b->kmode, b->fmode, ra.trace != nullptr, b->ellw, reps,
                                           tiles, to[c], to[c + 1] - to[c], t, ra),
                   "phase launch");
     }
-    hip_check(hsim::launch_site_finish(st, b->f64, b->kmode, b->fmode, ra.trace != nullptr, b->ellw, reps,
-                                       (const int32_t *)b->d_rep_tiles.p,
-                                       b->ngroups > 1 ? (const int32_t *)b->d_grp_reps[g].p : nullptr,
-                                       (int)b->grp_reps[g].size(), b->ncol_max, b->c_tail, t, ra),
-              "finish launch");
+    if (plain)
+        hip_check(hsim::launch_site_finish_plain(st, b->f64, b->kmode, b->fmode, ra.trace != nullptr, b->ellw, reps,
+                                                 (const hsim::SiteDesc *)b->d_site_desc.p,
+                                                 (const int32_t *)b->d_rep_tiles.p, rlist,
+                                                 (int)b->grp_reps[g].size(), b->ncol_max, b->c_tail, t, ra),
+                  "finish launch");
+    else
+        hip_check(hsim::launch_site_finish(st, b->f64, b->kmode, b->fmode, ra.trace != nullptr, b->ellw, reps,
+                                           (const int32_t *)b->d_rep_tiles.p, rlist, (int)b->grp_reps[g].size(),
+                                           b->ncol_max, b->c_tail, t, ra),
+                  "finish launch");
 }
 
 // Site layout: MCS t_off = 0..count-1 of a launch sequence starting at

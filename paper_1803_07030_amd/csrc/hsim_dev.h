@@ -63,6 +63,26 @@ struct Tile {
     int32_t nsl;   // padded-row slots that any site of the tile uses (its largest degree)
 };
 
+// What the plain model's update needs of a replica, in one record (site
+// layout, padded rows; float or double arrays), and a tile with its replica's
+// record: a block reads its tile's in one go instead of following the tile to
+// the replica and its fields one after the other.
+struct SiteDesc {
+    const int32_t *col;       // [ell_w][n] padded rows, slot-major
+    const void *J;            // [ell_w][n]
+    void *spins;              // [3][n_pad]
+    const uint32_t *orig;     // [n]
+    const void *k, *ax, *nd;  // K_SITE / F_SITE
+    double k0, e0[3], n0[3];
+    int32_t n, n_pad;
+    uint32_t rep_id;
+    int32_t rep;
+};
+struct TileDesc {
+    SiteDesc d;
+    int32_t begin, end, nsl, pad;
+};
+
 // Update policy of every site type.
 enum : int32_t { POL_RANDOM = 0, POL_FLIP = 1, POL_SMALL_STEP = 2, POL_GAUSSIAN = 3, POL_HN = 4,
                  POL_ADAPTIVE = 5 };
@@ -202,6 +222,14 @@ hipError_t launch_site_efull(hipStream_t st, bool f64, int kmode, int fmode, con
 hipError_t launch_site_finish(hipStream_t st, bool f64, int kmode, int fmode, bool trace, int ellw,
                               const RepDesc *reps, const int32_t *rep_tiles, const int32_t *rlist,
                               int nrep, int ncol_max, int c_tail, int t_off, const RunArgs &ra);
+// The same for the plain model (random moves, no cubic terms or spin lengths)
+// on padded rows.
+hipError_t launch_site_plain(hipStream_t st, bool f64, int kmode, int fmode, bool trace, int ellw,
+                             const TileDesc *tiles, int tile_off, int ntiles, int t_off, const RunArgs &ra);
+hipError_t launch_site_finish_plain(hipStream_t st, bool f64, int kmode, int fmode, bool trace, int ellw,
+                                    const RepDesc *reps, const SiteDesc *sites, const int32_t *rep_tiles,
+                                    const int32_t *rlist, int nrep, int ncol_max, int c_tail, int t_off,
+                                    const RunArgs &ra);
 hipError_t launch_ctl_advance(hipStream_t st, Ctl *ctl, uint32_t n);
 hipError_t launch_block_sweep(hipStream_t st, bool f64, int kmode, int fmode, bool trace,
                               int ellw, bool lds, int threads, size_t lds_bytes, const RepDesc *reps,

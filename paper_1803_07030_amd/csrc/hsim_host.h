@@ -189,6 +189,7 @@ struct hsim_batch_s {
     hsim::DevBuf d_tord;
 
     hsim::DevBuf d_reps, d_tiles, d_rep_tiles, d_rep_id;
+    hsim::DevBuf d_site_tiles, d_site_desc;   // site layout, plain model on padded rows
     bool tables_on_device = false;
 
     // binding
