@@ -446,22 +446,17 @@ __device__ __forceinline__ void rep_tile(const RepLaneArgs &a, const RepPhase &p
             rep_step_group<KM, FM, MAXD, VAR>(a, sp3, i, L.r, g, lp, active, ra, acc, nan);
     }
     if (nan) atomicOr(&ra.ctl->status, 1u);
+    // tile sums: a thread per (field, replica) adds the waves and lane groups
+    // in order
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) red[(L.w * 64 + L.lane) * NQ + q] = acc[q];
+    for (int q = 0; q < NQ; ++q) red[(q * kRepWaves + L.w) * 64 + L.lane] = acc[q];
     __syncthreads();
-    if (threadIdx.x < W) {
-        double v[NQ];
+    for (int e = threadIdx.x; e < NQ * W; e += kRepThreads) {
+        const int q = e / W, rl = e % W;
+        double v = 0.0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) v[q] = 0.0;
-        for (int ww = 0; ww < kRepWaves; ++ww)
-            for (int sb = 0; sb < 64 / W; ++sb)
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) v[q] += red[(ww * 64 + sb * W + (int)threadIdx.x) * NQ + q];
-        const int rr = (int)threadIdx.x + W * group;
-        const int tg = ph.tile0 + tile;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) part[((size_t)tg * kRecFields + q) * a.Rp + rr] = v[q];
-        if constexpr (POL) part[((size_t)tg * kRecFields + 6) * a.Rp + rr] = v[5];
+        for (int k = 0; k < kRepWaves * 64 / W; ++k) v += red[q * kRepWaves * 64 + k * W + rl];
+        part[((size_t)(ph.tile0 + tile) * kRecFields + (q == 5 ? 6 : q)) * a.Rp + rl + W * group] = v;
     }
     __syncthreads();
 }
