@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kMT) void k_mh_logd(int64_t tot, int n, int K, cons
 // No block waits for another and the host looks at the outcome once per
 // batch of launches; once done is set, later launches return at once.  An
 // iteration over 16 series of 2000 samples: 140 us with one block per k and a
-// copy to the host and back each time, 16 us now (30 us with the last block
+// copy to the host and back each time, 14 us now (30 us with the last block
 // to finish adding the sums behind a device-wide counter).
 // An exponent of -inf adds 0 (unless every one is -inf), NaN stays NaN.
 constexpr int kMhG = 16;             // lanes that add the blocks' sums of one k
@@ -416,23 +416,66 @@ __device__ __forceinline__ double mh_term(double v, double m)
     return m == -INFINITY ? (v == v ? 0.0 : v) : t;
 }
 
-// -ln of the sum over the nb blocks (p[b] = (m, s)), by 16 lanes; every lane
-// gets the result.
+// -ln of the sum over the nb blocks (p[b] = (m, s)), by G = 16 or 64 lanes;
+// every lane gets the result.
+template <int G>
 __device__ __forceinline__ double mh_combine(const double2 *p, int nb, int gl)
 {
+    auto all = [](double v, auto op) { return G == 16 ? row_all(v, op) : wave_all(v, op); };
     double m = -INFINITY, s = 0.0;
-    for (int q = gl; q < nb; q += kMhG) m = fmax(m, p[q].x);
-    m = row_all(m, OpMax());
-    for (int q = gl; q < nb; q += kMhG) s += p[q].x == -INFINITY ? p[q].y : p[q].y * exp(p[q].x - m);
-    s = row_all(s, OpAdd());
+    for (int q = gl; q < nb; q += G) m = fmax(m, p[q].x);
+    m = all(m, OpMax());
+    for (int q = gl; q < nb; q += G) s += p[q].x == -INFINITY ? p[q].y : p[q].y * exp(p[q].x - m);
+    s = all(s, OpAdd());
     return m == -INFINITY ? NAN : -(m + log(s));
 }
 
 __global__ __launch_bounds__(64) void k_mh_combine(int nb, const double2 *part, double *raw, const MhCtl *ctl)
 {
     if (ctl->done) return;
-    const double r = mh_combine(part + (size_t)blockIdx.x * nb, nb, threadIdx.x % kMhG);
+    const double r = mh_combine<kMhG>(part + (size_t)blockIdx.x * nb, nb, threadIdx.x % kMhG);
     if (threadIdx.x == 0) raw[blockIdx.x] = r;
+}
+
+// What launch j does first: completes iteration j and tests convergence; true
+// when the iterations are over.  The raw values are in shf (FUSED, added here
+// by G lanes per k) or raw (from k_mh_combine); f0: their shift.
+template <bool FUSED, int THREADS, int G>
+__device__ __forceinline__ bool mh_complete(int j, int K, int max_iter, double tol, double *fbuf,
+                                            const double *raw, const double2 *part, double *shf, MhCtl *ctl,
+                                            double &f0)
+{
+    // the outcome and f are fetched with the sums, not before them
+    const int over = ctl->done;
+    f0 = 0.0;
+    if (j == 0) return false;
+    const int lane = threadIdx.x & 63, nb = gridDim.x;
+    const double *prev = fbuf + (size_t)((j - 1) & 1) * K;
+    const double mine = prev[min(lane, K - 1)];
+    if constexpr (FUSED) {
+        const double2 *p = part + (size_t)((j - 1) & 1) * K * nb;
+        for (int k0 = 0; k0 < K; k0 += THREADS / G) {
+            const int k = k0 + (int)threadIdx.x / G;
+            const double r = mh_combine<G>(p + (size_t)min(k, K - 1) * nb, nb, threadIdx.x % G);
+            if (k < K && threadIdx.x % G == 0) shf[k] = r;
+        }
+        __syncthreads();
+    }
+    if (over) return true;
+    const double *rw = FUSED ? shf : raw;
+    double *next = fbuf + (size_t)(j & 1) * K;
+    f0 = rw[0];
+    double dmax = fmax(0.0, fabs(rw[min(lane, K - 1)] - f0 - mine));   // NaN counts as 0
+    for (int k = lane + 64; k < K; k += 64) dmax = fmax(dmax, fabs(rw[k] - f0 - prev[k]));
+    dmax = wave_all(dmax, OpMax());
+    if (blockIdx.x == 0)
+        for (int k = threadIdx.x; k < K; k += THREADS) next[k] = rw[k] - f0;
+    if (!(dmax < tol || j == max_iter)) return false;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->iters = j;
+        ctl->done = 1;
+    }
+    return true;
 }
 
 // fbuf [2][K]: f of iteration j in row j & 1; raw [K]: without the shift to
@@ -446,36 +489,9 @@ __global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, in
 {
     __shared__ double2 sh[kMhK][kMW];
     __shared__ double shf[FUSED ? kMhFusedK : 1];
-    if (ctl->done) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nb = gridDim.x;
-    double f0 = 0.0;
-    if (j > 0) {
-        if constexpr (FUSED) {
-            const double2 *p = part + (size_t)((j - 1) & 1) * K * nb;
-            for (int k0 = 0; k0 < K; k0 += kMT / kMhG) {
-                const int k = k0 + (int)threadIdx.x / kMhG;
-                const double r = mh_combine(p + (size_t)min(k, K - 1) * nb, nb, threadIdx.x % kMhG);
-                if (k < K && threadIdx.x % kMhG == 0) shf[k] = r;
-            }
-            __syncthreads();
-        }
-        const double *rw = FUSED ? shf : raw;
-        const double *prev = fbuf + (size_t)((j - 1) & 1) * K;
-        double *next = fbuf + (size_t)(j & 1) * K;
-        f0 = rw[0];
-        double dmax = 0.0;
-        for (int k = lane; k < K; k += 64) dmax = fmax(dmax, fabs(rw[k] - f0 - prev[k]));
-        dmax = wave_all(dmax, OpMax());
-        if (blockIdx.x == 0)
-            for (int k = threadIdx.x; k < K; k += kMT) next[k] = rw[k] - f0;
-        if (dmax < tol || j == max_iter) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
-                ctl->iters = j;
-                ctl->done = 1;
-            }
-            return;
-        }
-    }
+    double f0;
+    if (mh_complete<FUSED, kMT, kMhG>(j, K, max_iter, tol, fbuf, raw, part, shf, ctl, f0)) return;
     auto f = [&](int k) { return j > 0 ? (FUSED ? shf[k] : ((ConstD)raw)[k]) - f0 : 0.0; };
     const int64_t i0 = (int64_t)blockIdx.x * per, i1 = min(tot, i0 + per);
     const double ln_n = log((double)n);
@@ -539,6 +555,81 @@ __global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, in
             out[(size_t)(k0 + k) * nb + blockIdx.x] = make_double2(m, s);
         }
         __syncthreads();
+    }
+}
+
+// The same for kMhQuadMin + 1 .. kMhQuadK series and kMT samples per block,
+// all sums added by every block.  The K exponentials of a sample, twice, are a
+// chain that a thread per sample leaves the chip waiting for (125 blocks of 4
+// waves for 16 series of 2000 samples): here four neighbouring lanes share a
+// sample, each with every fourth k in registers, in blocks of 16 waves with as
+// many samples as before, so the sums to add do not get more (with four times
+// the blocks they did: 22 us an iteration).  A call with 16 series of 2000
+// samples: 7.43 -> 5.70 ms, 20 of 450: 11.6 -> 10.1, 9 of 1224: 1.82 -> 1.75;
+// with 5 of 550 the larger blocks cost more than they give, 0.53 -> 0.58 ms.
+constexpr int kMhQuadMin = 8, kMhQuadK = 32, kMhQ = 4;
+constexpr int kMQT = kMT * kMhQ, kMQW = kMQT / 64;
+
+__global__ __launch_bounds__(kMQT) void k_mh_iter_quad(int j, int64_t tot, int n, int K, int max_iter, double tol,
+                                                       const double *E, const double *beta_k, double *fbuf,
+                                                       double2 *part, MhCtl *ctl)
+{
+    constexpr int KQ = kMhQuadK / kMhQ;
+    __shared__ double2 sh[kMhQuadK][kMQW];
+    __shared__ double shf[kMhQuadK], shb[kMhQuadK];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nb = gridDim.x, ql = lane % kMhQ;
+    const int64_t i = (int64_t)blockIdx.x * kMT + threadIdx.x / kMhQ;
+    const bool mine = i < tot;
+    const double e = E[mine ? i : tot - 1], ln_n = log((double)n);
+    if ((int)threadIdx.x < K) shb[threadIdx.x] = beta_k[threadIdx.x];
+    double f0;
+    if (mh_complete<true, kMQT, 64>(j, K, max_iter, tol, fbuf, nullptr, part, shf, ctl, f0)) return;
+    __syncthreads();
+    // ln D; this lane's k are ql, ql + 4, ...: one past the end repeats the
+    // last and adds nothing
+    const int kq = (K + kMhQ - 1) / kMhQ;
+    double a[KQ], mx = -INFINITY, s = 0.0;
+#pragma unroll
+    for (int u = 0; u < KQ; ++u)
+        if (u < kq) {
+            const int k = min(u * kMhQ + ql, K - 1);
+            a[u] = ln_n + (j > 0 ? shf[k] - f0 : 0.0) - shb[k] * e;
+            mx = fmax(mx, a[u]);
+        }
+    mx = fmax(mx, dpp_move<0xB1>(mx));   // quad_perm [1,0,3,2]
+    mx = fmax(mx, dpp_move<0x4E>(mx));   // quad_perm [2,3,0,1]
+#pragma unroll
+    for (int u = 0; u < KQ; ++u)
+        if (u < kq) {
+            const double t = exp(a[u] - mx);
+            s += u * kMhQ + ql < K ? t : 0.0;
+        }
+    s += dpp_move<0xB1>(s);
+    s += dpp_move<0x4E>(s);
+    const double ld = mx + log(s);
+    double m[KQ];
+#pragma unroll
+    for (int u = 0; u < KQ; ++u)
+        if (u < kq) {
+            a[u] = -shb[min(u * kMhQ + ql, K - 1)] * e - ld;
+            m[u] = quarter_all(mine ? a[u] : -INFINITY, OpMax());
+        }
+#pragma unroll
+    for (int u = 0; u < KQ; ++u)
+        if (u < kq) {
+            const double t = mh_term(a[u], m[u]);
+            const double r = quarter_all(mine ? t : 0.0, OpAdd());
+            if (lane < kMhQ && u * kMhQ + ql < K) sh[u * kMhQ + ql][w] = make_double2(m[u], r);
+        }
+    __syncthreads();
+    // the waves' sums of a k, by a row of 16 lanes
+    const int k = (int)threadIdx.x / kMQW;
+    if (k < K) {
+        const double2 v = sh[k][threadIdx.x % kMQW];
+        const double mb = row_all(v.x, OpMax());
+        const double sb = row_all(v.x == -INFINITY ? v.y : v.y * exp(v.x - mb), OpAdd());
+        if (threadIdx.x % kMQW == 0)
+            part[(size_t)((j & 1) * K + k) * nb + blockIdx.x] = make_double2(mb, sb);
     }
 }
 
@@ -644,6 +735,7 @@ void analysis_multihist_impl(const double *d_hist, int32_t R, int32_t S, int32_t
     const int per = (int)((chunks + kMhBlocks - 1) / kMhBlocks) * kMT;
     const int nb = (int)((tot + per - 1) / per);
     const bool fused = K <= kMhFusedK && (int64_t)K * nb <= kMhFusedSums;
+    const bool quad = fused && per == kMT && K > kMhQuadMin && K <= kMhQuadK;
     // one allocation: E, |M| and ln D of every sample, the blocks' sums, f,
     // then the tables written from the host in one copy: the outcome and f
     // (zeros), the inverse temperatures, the series
@@ -681,8 +773,12 @@ void analysis_multihist_impl(const double *d_hist, int32_t R, int32_t S, int32_t
                 hipLaunchKernelGGL(k_mh_combine, dim3((unsigned)K), dim3(64), 0, st, nb,
                                    (const double2 *)(part + (size_t)((j - 1) & 1) * K * nb), raw,
                                    (const MhCtl *)ctl);
-            hipLaunchKernelGGL(iter, dim3((unsigned)nb), dim3(kMT), 0, st, j, tot, per, n, K, max_iter, tol,
-                               (const double *)E, bk, fbuf, (const double *)raw, logd, part, ctl);
+            if (quad)
+                hipLaunchKernelGGL(k_mh_iter_quad, dim3((unsigned)nb), dim3(kMQT), 0, st, j, tot, n, K, max_iter,
+                                   tol, (const double *)E, bk, fbuf, part, ctl);
+            else
+                hipLaunchKernelGGL(iter, dim3((unsigned)nb), dim3(kMT), 0, st, j, tot, per, n, K, max_iter, tol,
+                                   (const double *)E, bk, fbuf, (const double *)raw, logd, part, ctl);
         }
         hip_check(hipGetLastError(), "multihist launch");
         hip_check(hipMemcpyAsync(&now, ctl, sizeof now, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");

@@ -54,6 +54,16 @@ __device__ __forceinline__ double wave_all(double v, OP op)
     return swap_op<32>(swap_op<16>(row_all(v, op), op), op);
 }
 
+// op over the 16 lanes with the same lane number modulo 4; each gets the
+// result.
+template <typename OP>
+__device__ __forceinline__ double quarter_all(double v, OP op)
+{
+    v = op(v, dpp_move<0x124>(v));   // row_ror:4
+    v = op(v, dpp_move<0x128>(v));   // row_ror:8
+    return swap_op<32>(swap_op<16>(v, op), op);
+}
+
 struct OpAdd {
     __device__ __forceinline__ double operator()(double a, double b) const { return a + b; }
 };

@@ -98,3 +98,12 @@ def test_multihist_sizes(K, n, iters):
     for j, b in enumerate(ev):
         _close(out[j].cpu().numpy(), A.thermal_array(A.thermal(e, Mv, 64, b, logw=-b * e - logd)), rel=1e-8,
                floor=1e-10)
+
+
+# Around the numbers of series that have four lanes per sample, and around the
+# samples of a block.
+@pytest.mark.parametrize("K,n,iters", [(8, 32, 40), (9, 57, 40), (12, 64, 40), (31, 33, 40), (32, 120, 40),
+                                       (32, 129, 3),
+                                       (33, 31, 40)])
+def test_multihist_lanes_per_sample(K, n, iters):
+    test_multihist_sizes(K, n, iters)
