@@ -400,7 +400,8 @@ __global__ __launch_bounds__(kMT) void k_mh_logd(int64_t tot, int n, int K, cons
 // No block waits for another and the host looks at the outcome once per
 // batch of launches; once done is set, later launches return at once.  An
 // iteration over 16 series of 2000 samples: 140 us with one block per k and a
-// copy to the host and back each time, 14 us now (30 us with the last block
+// copy to the host and back each time, 14 us so (11 with four lanes per sample,
+// k_mh_iter_quad; 30 us with the last block
 // to finish adding the sums behind a device-wide counter).
 // An exponent of -inf adds 0 (unless every one is -inf), NaN stays NaN.
 constexpr int kMhG = 16;             // lanes that add the blocks' sums of one k
