@@ -447,7 +447,7 @@ __device__ __forceinline__ bool mh_complete(int j, int K, int max_iter, double t
                                             double &f0)
 {
     // the outcome and f are fetched with the sums, not before them
-    const int over = ctl->done;
+    int over = ctl->done;
     f0 = 0.0;
     if (j == 0) return false;
     const int lane = threadIdx.x & 63, nb = gridDim.x;
@@ -461,6 +461,15 @@ __device__ __forceinline__ bool mh_complete(int j, int K, int max_iter, double t
             if (k < K && threadIdx.x % G == 0) shf[k] = r;
         }
         __syncthreads();
+    } else {
+        // Thread 0, which may set the outcome below, reads it for the whole
+        // block: a wave that read it by itself could find it set by a faster
+        // one and leave before its share of next[] is written.  (With the
+        // sums added here the barrier above comes after every wave's read.)
+        __shared__ int was;
+        if (threadIdx.x == 0) was = over;
+        __syncthreads();
+        over = was;
     }
     if (over) return true;
     const double *rw = FUSED ? shf : raw;

@@ -107,3 +107,15 @@ def test_multihist_sizes(K, n, iters):
                                        (33, 31, 40)])
 def test_multihist_lanes_per_sample(K, n, iters):
     test_multihist_sizes(K, n, iters)
+
+
+# More series than a wave has lanes, their block sums added by a launch of
+# their own, stopped by the number of iterations: the last iteration's f is
+# complete for every series, the same in every call.
+@pytest.mark.parametrize("K,n,iters", [(65, 300, 6), (100, 200, 1), (100, 200, 7), (257, 17, 4)])
+def test_multihist_stopped_by_iterations(K, n, iters):
+    test_multihist_sizes(K, n, iters)
+    h, beta = _history(K, 1, n, seed=K)
+    args = (torch.tensor(h, device="cuda"), 0, 64, [(k, 0) for k in range(K)], beta[:, 0], beta[:1, 0])
+    f = [hsim.hsim_analysis_multihist(*args, max_iter=iters, tol=1e-9)[0] for _ in range(20)]
+    assert all(np.array_equal(f[0], x) for x in f)
