@@ -351,17 +351,39 @@ struct MhCtl {
     int32_t done, iters;
 };
 
-// Energies and |M| of the K series, series after series.
-__global__ __launch_bounds__(kMT) void k_mh_gather(const double *hist, const int32_t *rs, int S, int M,
-                                                   int m0, int n, int64_t tot, double *E, double *A)
+// The samples of the K series, series after series: energies and |M| copied
+// side by side (COPY), or read in the history, where calls of many samples
+// need no memory for the copies (16 bytes each, beside ln D's 8).
+template <bool COPY>
+struct MhSamples {
+    const double *copy_E, *copy_A;
+    const double *hist;
+    const int32_t *rs;      // [K][2] (replica, step)
+    int S, M, m0, n;
+    __device__ __forceinline__ double E(int64_t i) const
+    {
+        if constexpr (COPY) return copy_E[i];
+        const int64_t k = i / n;
+        return series(k).E((int)(i - k * n));
+    }
+    __device__ __forceinline__ double A(int64_t i) const
+    {
+        if constexpr (COPY) return copy_A[i];
+        const int64_t k = i / n;
+        return series(k).A((int)(i - k * n));
+    }
+    __device__ __forceinline__ Series series(int64_t k) const
+    {
+        return Series(hist, (int64_t)rs[2 * k] * S + rs[2 * k + 1], M, m0);
+    }
+};
+
+__global__ __launch_bounds__(kMT) void k_mh_gather(MhSamples<false> sm, int64_t tot, double *E, double *A)
 {
     const int64_t i = (int64_t)blockIdx.x * kMT + threadIdx.x;
     if (i >= tot) return;
-    const int64_t k = i / n;
-    const int m = (int)(i - k * n);
-    const Series sr(hist, (int64_t)rs[2 * k] * S + rs[2 * k + 1], M, m0);
-    E[i] = sr.E(m);
-    A[i] = sr.A(m);
+    E[i] = sm.E(i);
+    A[i] = sm.A(i);
 }
 
 // Tables no thread of the launch writes, read through the constant address
@@ -381,12 +403,13 @@ __device__ __forceinline__ double mh_logd(double e, double ln_n, int K, ConstD b
     return mx + log(s);
 }
 
-__global__ __launch_bounds__(kMT) void k_mh_logd(int64_t tot, int n, int K, const double *E,
-                                                 const double *beta_k, const double *f, double *logd)
+template <bool COPY>
+__global__ __launch_bounds__(kMT) void k_mh_logd(int64_t tot, int K, MhSamples<COPY> sm, const double *beta_k,
+                                                 const double *f, double *logd)
 {
     const int64_t i = (int64_t)blockIdx.x * kMT + threadIdx.x;
     if (i < tot)
-        logd[i] = mh_logd(E[i], log((double)n), K, (ConstD)beta_k, [&](int j) { return ((ConstD)f)[j]; });
+        logd[i] = mh_logd(sm.E(i), log((double)sm.n), K, (ConstD)beta_k, [&](int j) { return ((ConstD)f)[j]; });
 }
 
 // The self-consistent equations
@@ -491,11 +514,10 @@ __device__ __forceinline__ bool mh_complete(int j, int K, int max_iter, double t
 // fbuf [2][K]: f of iteration j in row j & 1; raw [K]: without the shift to
 // f_0 = 0 (from k_mh_combine, not FUSED); part [2][K][blocks].  ONE: per ==
 // kMT, one sample per thread.
-template <bool FUSED, bool ONE>
-__global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, int n, int K, int max_iter,
-                                                 double tol, const double *E, const double *beta_k,
-                                                 double *fbuf, const double *raw, double *logd,
-                                                 double2 *part, MhCtl *ctl)
+template <bool FUSED, bool ONE, bool COPY>
+__global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, int K, int max_iter, double tol,
+                                                 MhSamples<COPY> sm, const double *beta_k, double *fbuf,
+                                                 const double *raw, double *logd, double2 *part, MhCtl *ctl)
 {
     __shared__ double2 sh[kMhK][kMW];
     __shared__ double shf[FUSED ? kMhFusedK : 1];
@@ -504,17 +526,17 @@ __global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, in
     if (mh_complete<FUSED, kMT, kMhG>(j, K, max_iter, tol, fbuf, raw, part, shf, ctl, f0)) return;
     auto f = [&](int k) { return j > 0 ? (FUSED ? shf[k] : ((ConstD)raw)[k]) - f0 : 0.0; };
     const int64_t i0 = (int64_t)blockIdx.x * per, i1 = min(tot, i0 + per);
-    const double ln_n = log((double)n);
+    const double ln_n = log((double)sm.n);
     // a thread's own samples: i0 + threadIdx.x, + kMT, ...; the first stays in
     // registers
     const int64_t mine = i0 + threadIdx.x;
     double e = 0.0, ld = 0.0;
     if (mine < i1) {
-        e = E[mine];
+        e = sm.E(mine);
         ld = mh_logd(e, ln_n, K, (ConstD)beta_k, f);
     }
     if constexpr (!ONE)
-        for (int64_t i = mine + kMT; i < i1; i += kMT) logd[i] = mh_logd(E[i], ln_n, K, (ConstD)beta_k, f);
+        for (int64_t i = mine + kMT; i < i1; i += kMT) logd[i] = mh_logd(sm.E(i), ln_n, K, (ConstD)beta_k, f);
     double2 *out = part + (size_t)(j & 1) * K * nb;
     for (int k0 = 0; k0 < K; k0 += kMhK) {
         const int kn = min(kMhK, K - k0);
@@ -545,10 +567,10 @@ __global__ __launch_bounds__(kMT) void k_mh_iter(int j, int64_t tot, int per, in
             for (int k = 0; k < kn; ++k) {
                 const double b = ((ConstD)beta_k)[k0 + k], v0 = -b * e - ld;
                 double m = mine < i1 ? v0 : -INFINITY;
-                for (int64_t i = mine + kMT; i < i1; i += kMT) m = fmax(m, -b * E[i] - logd[i]);
+                for (int64_t i = mine + kMT; i < i1; i += kMT) m = fmax(m, -b * sm.E(i) - logd[i]);
                 m = wave_all(m, OpMax());
                 double s = mine < i1 ? mh_term(v0, m) : 0.0;
-                for (int64_t i = mine + kMT; i < i1; i += kMT) s += mh_term(-b * E[i] - logd[i], m);
+                for (int64_t i = mine + kMT; i < i1; i += kMT) s += mh_term(-b * sm.E(i) - logd[i], m);
                 s = wave_all(s, OpAdd());
                 if (lane == 0) sh[k][w] = make_double2(m, s);
             }
@@ -645,15 +667,16 @@ __global__ __launch_bounds__(kMQT) void k_mh_iter_quad(int j, int64_t tot, int n
 
 // Thermal summary at beta_eval[j] from all samples of the K series with
 // weights exp(-beta E - ln D).
-__global__ __launch_bounds__(kAT) void k_mh_thermal(int64_t tot, double N, const double *E, const double *A,
-                                                    const double *logd, const double *beta_eval, double *out)
+template <bool COPY>
+__global__ __launch_bounds__(kAT) void k_mh_thermal(int64_t tot, double N, MhSamples<COPY> sm, const double *logd,
+                                                    const double *beta_eval, double *out)
 {
     __shared__ double lds[kAW * 5];
     const int j = blockIdx.x;
     const double b = beta_eval[j];
     auto get = [&](int64_t i, double &e, double &a) {
-        e = E[i];
-        a = A[i];
+        e = sm.E(i);
+        a = sm.A(i);
     };
     auto logw = [&](int64_t i, double e) { return -b * e - logd[i]; };
     thermal_block<0>(tot, get, logw, N, b, lds, out + (size_t)j * 9);
@@ -746,8 +769,17 @@ void analysis_multihist_impl(const double *d_hist, int32_t R, int32_t S, int32_t
     const int nb = (int)((tot + per - 1) / per);
     const bool fused = K <= kMhFusedK && (int64_t)K * nb <= kMhFusedSums;
     const bool quad = fused && per == kMT && K > kMhQuadMin && K <= kMhQuadK;
-    // one allocation: E, |M| and ln D of every sample, the blocks' sums, f,
-    // then the tables written from the host in one copy: the outcome and f
+    // Energies and |M| are copied side by side (of 900,000 samples, read by
+    // every k of an iteration) as long as the copies take at most a quarter
+    // of the memory that is free; at one sample per thread they are 2 MB.
+    bool copy = per == kMT;
+    if (!copy) {
+        size_t free_bytes = 0, total_bytes = 0;
+        hip_check(hipMemGetInfo(&free_bytes, &total_bytes), "hipMemGetInfo");
+        copy = 16 * (size_t)tot <= free_bytes / 4;
+    }
+    // one allocation: the copies and ln D of every sample, the blocks' sums,
+    // f, then the tables written from the host in one copy: the outcome and f
     // (zeros), the inverse temperatures, the series
     static_assert(sizeof(MhCtl) == sizeof(double), "the outcome takes one word");
     std::vector<double> tab(1 + 4 * (size_t)K + (size_t)n_eval, 0.0);
@@ -755,50 +787,61 @@ void analysis_multihist_impl(const double *d_hist, int32_t R, int32_t S, int32_t
     std::copy(beta_k, beta_k + K, h);
     if (n_eval > 0) std::copy(beta_eval, beta_eval + n_eval, h + K);
     std::memcpy(h + K + n_eval, rs.data(), (size_t)K * 8);
-    const size_t samples = 3 * (size_t)tot + (tot & 1);      // even: the sums are 16-byte aligned
+    const size_t samples = (copy ? 3 : 1) * (size_t)tot + (tot & 1);   // even: the sums are 16-byte aligned
     const size_t sums = 4 * (size_t)K * nb;
     DevBuf buf;
-    auto *E = (double *)buf.alloc((samples + sums + K + tab.size()) * 8);
-    double *A = E + tot, *logd = A + tot;
-    auto *part = (double2 *)(E + samples);
-    double *raw = E + samples + sums, *d_tab = raw + K;
+    auto *logd = (double *)buf.alloc((samples + sums + K + tab.size()) * 8);
+    double *E = copy ? logd + tot : nullptr, *A = copy ? E + tot : nullptr;
+    auto *part = (double2 *)(logd + samples);
+    double *raw = logd + samples + sums, *d_tab = raw + K;
     auto *ctl = (MhCtl *)d_tab;
     double *fbuf = d_tab + 1;
     const double *bk = fbuf + 2 * (size_t)K, *be = bk + K;
     const auto *d_rs = (const int32_t *)(be + n_eval);
     hip_check(hipMemcpyAsync(d_tab, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
     const dim3 all((unsigned)chunks);
-    hipLaunchKernelGGL(k_mh_gather, all, dim3(kMT), 0, st, d_hist, d_rs, S, M, m0, n, tot, E, A);
+    const MhSamples<false> sm{nullptr, nullptr, d_hist, d_rs, S, M, m0, n};
+    const MhSamples<true> smc{E, A, d_hist, d_rs, S, M, m0, n};
+    if (copy) hipLaunchKernelGGL(k_mh_gather, all, dim3(kMT), 0, st, sm, tot, E, A);
+    // launch j of the iterations
+    auto launch = [&](auto kernel, const auto &src, int j) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kMT), 0, st, j, tot, per, K, max_iter, tol, src, bk,
+                           fbuf, (const double *)raw, logd, part, ctl);
+    };
+    auto iterate = [&](int j) {
+        if (!fused && j > 0)
+            hipLaunchKernelGGL(k_mh_combine, dim3((unsigned)K), dim3(64), 0, st, nb,
+                               (const double2 *)(part + (size_t)((j - 1) & 1) * K * nb), raw, (const MhCtl *)ctl);
+        if (quad)
+            hipLaunchKernelGGL(k_mh_iter_quad, dim3((unsigned)nb), dim3(kMQT), 0, st, j, tot, n, K, max_iter, tol,
+                               (const double *)E, bk, fbuf, part, ctl);
+        else if (per == kMT)
+            launch(fused ? k_mh_iter<true, true, true> : k_mh_iter<false, true, true>, smc, j);
+        else if (copy)
+            launch(fused ? k_mh_iter<true, false, true> : k_mh_iter<false, false, true>, smc, j);
+        else
+            launch(fused ? k_mh_iter<true, false, false> : k_mh_iter<false, false, false>, sm, j);
+    };
     // iterations are enqueued in growing batches (launch j completes
     // iteration j, so max_iter iterations take max_iter + 1 launches)
-    auto iter = fused ? (per == kMT ? k_mh_iter<true, true> : k_mh_iter<true, false>)
-                      : (per == kMT ? k_mh_iter<false, true> : k_mh_iter<false, false>);
     MhCtl now{};
     int64_t sent = 0;
     for (int batch = 8; !now.done; batch = std::min(2 * batch, 64)) {
         const int64_t end = std::min<int64_t>(sent + batch, (int64_t)max_iter + 1);
-        for (; sent < end; ++sent) {
-            const int j = (int)sent;
-            if (!fused && j > 0)
-                hipLaunchKernelGGL(k_mh_combine, dim3((unsigned)K), dim3(64), 0, st, nb,
-                                   (const double2 *)(part + (size_t)((j - 1) & 1) * K * nb), raw,
-                                   (const MhCtl *)ctl);
-            if (quad)
-                hipLaunchKernelGGL(k_mh_iter_quad, dim3((unsigned)nb), dim3(kMQT), 0, st, j, tot, n, K, max_iter,
-                                   tol, (const double *)E, bk, fbuf, part, ctl);
-            else
-                hipLaunchKernelGGL(iter, dim3((unsigned)nb), dim3(kMT), 0, st, j, tot, per, n, K, max_iter, tol,
-                                   (const double *)E, bk, fbuf, (const double *)raw, logd, part, ctl);
-        }
+        for (; sent < end; ++sent) iterate((int)sent);
         hip_check(hipGetLastError(), "multihist launch");
         hip_check(hipMemcpyAsync(&now, ctl, sizeof now, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
         hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
     }
     const double *f = fbuf + (size_t)(now.iters & 1) * K;
+    auto evaluate = [&](auto logd_kernel, auto thermal_kernel, const auto &src) {
+        hipLaunchKernelGGL(logd_kernel, all, dim3(kMT), 0, st, tot, K, src, bk, f, logd);
+        hipLaunchKernelGGL(thermal_kernel, dim3((unsigned)n_eval), dim3(kAT), 0, st, tot, (double)n_sites, src,
+                           (const double *)logd, be, d_out);
+    };
     if (n_eval > 0) {
-        hipLaunchKernelGGL(k_mh_logd, all, dim3(kMT), 0, st, tot, n, K, (const double *)E, bk, f, logd);
-        hipLaunchKernelGGL(k_mh_thermal, dim3((unsigned)n_eval), dim3(kAT), 0, st, tot, (double)n_sites,
-                           (const double *)E, (const double *)A, (const double *)logd, be, d_out);
+        if (copy) evaluate(k_mh_logd<true>, k_mh_thermal<true>, smc);
+        else evaluate(k_mh_logd<false>, k_mh_thermal<false>, sm);
     }
     hip_check(hipGetLastError(), "multihist launch");
     hip_check(hipMemcpyAsync(f_out, f, (size_t)K * 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");

@@ -119,3 +119,30 @@ def test_multihist_stopped_by_iterations(K, n, iters):
     args = (torch.tensor(h, device="cuda"), 0, 64, [(k, 0) for k in range(K)], beta[:, 0], beta[:1, 0])
     f = [hsim.hsim_analysis_multihist(*args, max_iter=iters, tol=1e-9)[0] for _ in range(20)]
     assert all(np.array_equal(f[0], x) for x in f)
+
+
+# On a card that is nearly full, energies and |M| are read in the history
+# instead of from copies: a call that has room for 8 bytes per sample and no
+# more gives the same bits.  The same series stands for every temperature, so
+# the samples outnumber the history.
+@pytest.mark.parametrize("K", [8, 9])
+def test_multihist_without_room_for_copies(K):
+    n, room = 1 << 22, 500 << 20                 # 268 or 302 MB for ln D, three times as much with copies
+    g = torch.Generator(device="cuda").manual_seed(3)
+    h = torch.randn(1, 1, n, 5, generator=g, device="cuda", dtype=torch.float64) * 8.0 + 20.0
+    bk = 0.3 + 0.01 * np.arange(K)
+    args = (h, 0, 64, [(0, 0)] * K, bk, bk[:3])
+    want = hsim.hsim_analysis_multihist(*args, max_iter=3, tol=1e-30)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    try:
+        while (left := torch.cuda.mem_get_info()[0] - room) > 1 << 20:
+            held.append(torch.empty(min(left, 16 << 30), dtype=torch.uint8, device="cuda"))
+        got = hsim.hsim_analysis_multihist(*args, max_iter=3, tol=1e-30)
+        torch.cuda.synchronize()
+    finally:
+        held.clear()
+        torch.cuda.empty_cache()
+    assert got[1] == want[1] == 3
+    assert np.array_equal(got[0], want[0]) and torch.equal(got[2], want[2])
