@@ -22,18 +22,18 @@ namespace hsim {
 
 namespace {
 
-constexpr int kAT = 1024;            // threads of the per-series blocks
-constexpr int kAW = kAT / 64;
+constexpr int kAT = 1024;            // threads of the per-series blocks, at most
 constexpr int kMT = 256;             // threads of the multiple-histogram blocks
 constexpr int kMW = kMT / 64;
 
 // Block-wide sums of NV values (fixed order: a tree over each wave, then the
-// waves in order); every thread gets the results.  lds: kAW * NV doubles.
-template <int NV>
+// waves in order); every thread gets the results.  lds: NT / 64 * NV doubles.
+template <int NV, int NT>
 __device__ __forceinline__ void block_sums(double (&v)[NV], double *lds)
 {
 #pragma unroll
     for (int q = 0; q < NV; ++q) v[q] = wave_all(v[q], OpAdd());
+    if constexpr (NT == 64) return;
     const int w = threadIdx.x >> 6;
     __syncthreads();                 // the previous use of lds is over
     if ((threadIdx.x & 63) == 0)
@@ -44,20 +44,22 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double *lds)
     for (int q = 0; q < NV; ++q) {
         double t = lds[q];
 #pragma unroll
-        for (int k = 1; k < kAW; ++k) t += lds[k * NV + q];
+        for (int k = 1; k < NT / 64; ++k) t += lds[k * NV + q];
         v[q] = t;
     }
 }
 
+template <int NT>
 __device__ __forceinline__ double block_max(double v, double *lds)
 {
     v = wave_all(v, OpMax());
+    if constexpr (NT == 64) return v;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
     __syncthreads();
     double t = lds[0];
 #pragma unroll
-    for (int k = 1; k < kAW; ++k) t = fmax(t, lds[k]);
+    for (int k = 1; k < NT / 64; ++k) t = fmax(t, lds[k]);
     return t;
 }
 
@@ -80,7 +82,7 @@ struct Series {
 // most K samples per thread, held in registers between the three passes (the
 // weights' maximum, the means, the central moments); K = 0: any count, read
 // again by each pass.
-template <int K, typename GET, typename LW>
+template <int K, int NT, typename GET, typename LW>
 __device__ __forceinline__ void thermal_block(int64_t count, GET get, LW logw, double N, double beta,
                                               double *lds, double *out)
 {
@@ -89,23 +91,23 @@ __device__ __forceinline__ void thermal_block(int64_t count, GET get, LW logw, d
     if constexpr (K > 0) {
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int i = (int)threadIdx.x + j * kAT;
+            const int i = (int)threadIdx.x + j * NT;
             e[j] = 0.0;
             a[j] = 0.0;
             if (i < count) get(i, e[j], a[j]);
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int i = (int)threadIdx.x + j * kAT;
+            const int i = (int)threadIdx.x + j * NT;
             mx = i < count ? fmax(mx, logw(i, e[j])) : mx;
         }
     } else {
-        for (int64_t i = threadIdx.x; i < count; i += kAT) {
+        for (int64_t i = threadIdx.x; i < count; i += NT) {
             get(i, e[0], a[0]);
             mx = fmax(mx, logw(i, e[0]));
         }
     }
-    mx = block_max(mx, lds);
+    mx = block_max<NT>(mx, lds);
     double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     auto first = [&](double wi, double ei, double ai) {
         const double a2 = ai * ai;
@@ -118,17 +120,17 @@ __device__ __forceinline__ void thermal_block(int64_t count, GET get, LW logw, d
     if constexpr (K > 0) {
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int i = (int)threadIdx.x + j * kAT;
+            const int i = (int)threadIdx.x + j * NT;
             if (i < count) first(exp(logw(i, e[j]) - mx), e[j], a[j]);
             __builtin_amdgcn_sched_barrier(0);   // one exponential's registers at a time
         }
     } else {
-        for (int64_t i = threadIdx.x; i < count; i += kAT) {
+        for (int64_t i = threadIdx.x; i < count; i += NT) {
             get(i, e[0], a[0]);
             first(exp(logw(i, e[0]) - mx), e[0], a[0]);
         }
     }
-    block_sums<5>(s, lds);
+    block_sums<5, NT>(s, lds);
     const double W = s[0], mE = s[1] / W, mA = s[2] / W, mA2 = s[3] / W, mA4 = s[4] / W;
     double c[4] = {0.0, 0.0, 0.0, 0.0};
     auto second = [&](double wi, double ei, double ai) {
@@ -141,17 +143,17 @@ __device__ __forceinline__ void thermal_block(int64_t count, GET get, LW logw, d
     if constexpr (K > 0) {
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int i = (int)threadIdx.x + j * kAT;
+            const int i = (int)threadIdx.x + j * NT;
             if (i < count) second(exp(logw(i, e[j]) - mx), e[j], a[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        for (int64_t i = threadIdx.x; i < count; i += kAT) {
+        for (int64_t i = threadIdx.x; i < count; i += NT) {
             get(i, e[0], a[0]);
             second(exp(logw(i, e[0]) - mx), e[0], a[0]);
         }
     }
-    block_sums<4>(c, lds);
+    block_sums<4, NT>(c, lds);
     if (threadIdx.x == 0) {
         const double vE = c[0] / W, vA = c[1] / W, c1 = c[2] / W, c2 = c[3] / W;
         const double m2 = mA2 / (N * N), m4 = mA4 / (N * N * N * N);
@@ -177,16 +179,21 @@ struct BetaTable {
 };
 
 // grid (series, n_eval): series t at its sampling beta, evaluated with weights
-// exp(-(beta - beta0) E).  One block per evaluation, bounded by latency: a
-// series of up to 12 * 1024 samples (what 128 registers per thread hold) is
-// read once and stays in registers, a longer one is read by each of the three
-// passes.  64 series of 9000 samples at 3 betas: 65.6 us with 256 threads
-// that read it three times, 26 us now.
-template <int K, bool ARG>
-__global__ __launch_bounds__(kAT) void k_thermal(const double *hist, int M, int m0, int n, double N,
+// exp(-(beta - beta0) E).  One block per evaluation, bounded by latency where
+// series are few: one of up to 12 * 1024 samples is read once and kept by the
+// threads between the three passes (4 samples per thread in registers; of 12,
+// under the 128 registers of 1024 threads, a part in scratch, 196 bytes per
+// lane), a longer one is read by each pass.  64 series of 9000 samples at 3
+// betas: 65.6 us with 256 threads that read it three times, 26 us now.  Where
+// series are many and short, threads without a sample cost as much as others,
+// so a block is no larger than 4 samples per thread ask for: 12832 series of
+// 50 samples at 3 betas: 939 us in blocks of 1024 threads, 150 in blocks of 64
+// (370 in blocks of 256 that read three times).
+template <int K, int NT, bool ARG>
+__global__ __launch_bounds__(NT) void k_thermal(const double *hist, int M, int m0, int n, double N,
                                                  const double *tab, BetaTable bt, int n_eval, double *out)
 {
-    __shared__ double lds[kAW * 5];
+    __shared__ double lds[NT / 64 * 5];
     const int t = blockIdx.x, j = blockIdx.y;
     const size_t row = (size_t)t * (1 + n_eval);
     const double b0 = ARG ? bt.v[row] : tab[row], b = ARG ? bt.v[row + 1 + j] : tab[row + 1 + j];
@@ -197,7 +204,7 @@ __global__ __launch_bounds__(kAT) void k_thermal(const double *hist, int M, int 
         a = sr.A((int)i);
     };
     auto logw = [&](int64_t, double e) { return db == 0.0 ? 0.0 : -db * e; };
-    thermal_block<K>(n, get, logw, N, b, lds, out + ((size_t)t * n_eval + j) * 9);
+    thermal_block<K, NT>(n, get, logw, N, b, lds, out + ((size_t)t * n_eval + j) * 9);
 }
 
 // Integrated autocorrelation time of series t (observable 0: E, 1: |M|) with
@@ -212,16 +219,18 @@ __global__ __launch_bounds__(kAT) void k_thermal(const double *hist, int M, int 
 // longer ones pass through it in segments.  64 series of 9000 samples with
 // windows of up to 240 lags: 9.4 ms with one thread per lag walking the whole
 // series in global memory, 60 us now.
-constexpr int kLagW = 8, kLags = kAW * kLagW;
+constexpr int kLagW = 8;             // lags per wave
 constexpr int kTauRes = 18432;       // samples of a resident series (144 KiB of LDS)
 constexpr int kTauSeg = 8192;        // samples of a segment otherwise
 
 // pad: zeros held behind a resident series.
-__global__ __launch_bounds__(kAT) void k_tau(const double *hist, int M, int m0, int n, int pad, int obs, double c,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_tau(const double *hist, int M, int m0, int n, int pad, int obs, double c,
                                              double *tau_out, int32_t *win_out)
 {
     extern __shared__ double dyn[];
-    __shared__ double lds[kAW];
+    constexpr int kLags = NT / 64 * kLagW;   // lags at a time
+    __shared__ double lds[NT / 64];
     __shared__ double rho[kLags];
     __shared__ int done;
     const int t = blockIdx.x;
@@ -229,21 +238,21 @@ __global__ __launch_bounds__(kAT) void k_tau(const double *hist, int M, int m0, 
     auto x = [&](int m) { return obs == 0 ? sr.E(m) : sr.A(m); };
     const bool res = n <= kTauRes;
     double s[1] = {0.0};
-    for (int m = threadIdx.x; m < n; m += kAT) {
+    for (int m = threadIdx.x; m < n; m += NT) {
         const double v = x(m);
         if (res) dyn[m] = v;
         s[0] += v;
     }
-    for (int m = threadIdx.x; m < pad; m += kAT) dyn[n + m] = 0.0;
-    block_sums<1>(s, lds);
+    for (int m = threadIdx.x; m < pad; m += NT) dyn[n + m] = 0.0;
+    block_sums<1, NT>(s, lds);
     const double mean = s[0] / n;
     double q[1] = {0.0};
-    for (int m = threadIdx.x; m < n; m += kAT) {
+    for (int m = threadIdx.x; m < n; m += NT) {
         const double d = (res ? dyn[m] : x(m)) - mean;
         if (res) dyn[m] = d;
         q[0] += d * d;
     }
-    block_sums<1>(q, lds);
+    block_sums<1, NT>(q, lds);
     const double c0 = q[0] / n;
     double tau = 0.5;
     int win = n / 2;
@@ -262,8 +271,8 @@ __global__ __launch_bounds__(kAT) void k_tau(const double *hist, int M, int m0, 
             const double *A = dyn, *B = res ? dyn + base : dyn + kTauSeg;
             if (!res) {
                 __syncthreads();
-                for (int m = threadIdx.x; m < la; m += kAT) dyn[m] = x(s0 + m) - mean;
-                for (int m = threadIdx.x; m < lb; m += kAT) dyn[kTauSeg + m] = x(s0 + base + m) - mean;
+                for (int m = threadIdx.x; m < la; m += NT) dyn[m] = x(s0 + m) - mean;
+                for (int m = threadIdx.x; m < lb; m += NT) dyn[kTauSeg + m] = x(s0 + base + m) - mean;
                 __syncthreads();
             }
             const int run = ((la + 63) / 64) | 1;
@@ -320,14 +329,15 @@ __global__ __launch_bounds__(kAT) void k_tau(const double *hist, int M, int m0, 
             // tau up to each lag: a scan over the lanes, 64 lags at a time
             for (int h = 0; h < kLags && base + h <= n / 2; h += 64) {
                 const int lag = base + h + lane;
-                double p = lag <= n / 2 ? rho[h + lane] : 0.0;
+                const bool in = h + lane < kLags && lag <= n / 2;
+                double p = in ? rho[h + lane] : 0.0;
 #pragma unroll
                 for (int o = 1; o < 64; o <<= 1) {
                     const double q = __shfl_up(p, o, 64);
                     p = lane >= o ? p + q : p;
                 }
                 const double tl = tau + p;
-                const unsigned long long hit = __ballot(lag <= n / 2 && lag >= c * tl);
+                const unsigned long long hit = __ballot(in && lag >= c * tl);
                 const int at = hit ? __ffsll(hit) - 1 : 63;
                 tau = __shfl(tl, at, 64);
                 if (hit) {
@@ -671,7 +681,7 @@ template <bool COPY>
 __global__ __launch_bounds__(kAT) void k_mh_thermal(int64_t tot, double N, MhSamples<COPY> sm, const double *logd,
                                                     const double *beta_eval, double *out)
 {
-    __shared__ double lds[kAW * 5];
+    __shared__ double lds[kAT / 64 * 5];
     const int j = blockIdx.x;
     const double b = beta_eval[j];
     auto get = [&](int64_t i, double &e, double &a) {
@@ -679,7 +689,7 @@ __global__ __launch_bounds__(kAT) void k_mh_thermal(int64_t tot, double N, MhSam
         a = sm.A(i);
     };
     auto logw = [&](int64_t i, double e) { return -b * e - logd[i]; };
-    thermal_block<0>(tot, get, logw, N, b, lds, out + (size_t)j * 9);
+    thermal_block<0, kAT>(tot, get, logw, N, b, lds, out + (size_t)j * 9);
 }
 
 void check_hist(const double *h, int32_t R, int32_t S, int32_t M, int32_t m0)
@@ -715,14 +725,16 @@ void analysis_thermal_impl(const double *d_hist, int32_t R, int32_t S, int32_t M
     if (arg) std::copy(tab.begin(), tab.end(), bt.v);
     else d_tab.upload(tab);
     const int n = M - m0;
-    const dim3 grid((unsigned)T, (unsigned)n_eval), blk(kAT);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, blk, 0, st, d_hist, M, m0, n, (double)n_sites, (const double *)d_tab.p, bt,
+    const dim3 grid((unsigned)T, (unsigned)n_eval);
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, d_hist, M, m0, n, (double)n_sites, (const double *)d_tab.p, bt,
                            n_eval, d_out);
     };
-    if (n <= 4 * kAT) launch(arg ? k_thermal<4, true> : k_thermal<4, false>);
-    else if (n <= 12 * kAT) launch(arg ? k_thermal<12, true> : k_thermal<12, false>);
-    else launch(arg ? k_thermal<0, true> : k_thermal<0, false>);
+    if (n <= 4 * 64) launch(arg ? k_thermal<4, 64, true> : k_thermal<4, 64, false>, 64);
+    else if (n <= 4 * 256) launch(arg ? k_thermal<4, 256, true> : k_thermal<4, 256, false>, 256);
+    else if (n <= 4 * kAT) launch(arg ? k_thermal<4, kAT, true> : k_thermal<4, kAT, false>, kAT);
+    else if (n <= 12 * kAT) launch(arg ? k_thermal<12, kAT, true> : k_thermal<12, kAT, false>, kAT);
+    else launch(arg ? k_thermal<0, kAT, true> : k_thermal<0, kAT, false>, kAT);
     hip_check(hipGetLastError(), "thermal launch");
     hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");   // before the table is freed
 }
@@ -733,13 +745,24 @@ void analysis_tau_impl(const double *d_hist, int32_t R, int32_t S, int32_t M, in
     check_hist(d_hist, R, S, M, m0);
     if ((obs != 0 && obs != 1) || !(c > 0.0) || !d_tau) throw Error(HSIM_E_ARG, "analysis_tau: bad argument");
     const int n = M - m0;
-    const int pad = n <= kTauRes ? std::min(n / 2 + 2 * kLags, kTauRes - n) : 0;
-    const size_t dyn = (n <= kTauRes ? (size_t)(n + pad) : (size_t)(2 * kTauSeg + kLags)) * sizeof(double);
-    if (dyn > 65536)
-        hip_check(hipFuncSetAttribute((const void *)k_tau, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn),
-                  "hipFuncSetAttribute");
-    hipLaunchKernelGGL(k_tau, dim3((unsigned)(R * S)), dim3(kAT), dyn, st, d_hist, M, m0, n, pad, obs, c, d_tau,
-                       d_win);
+    auto launch = [&](auto kernel, int threads) {
+        const int lags = threads / 64 * kLagW;
+        const int pad = n <= kTauRes ? std::min(n / 2 + 2 * lags, kTauRes - n) : 0;
+        const size_t dyn = (n <= kTauRes ? (size_t)(n + pad) : (size_t)(2 * kTauSeg + lags)) * sizeof(double);
+        if (dyn > 65536)
+            hip_check(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn),
+                      "hipFuncSetAttribute");
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(R * S)), dim3((unsigned)threads), dyn, st, d_hist, M, m0, n, pad,
+                           obs, c, d_tau, d_win);
+    };
+    // Blocks of 256 threads where there are more series than CUs and a block's
+    // LDS leaves room for six of them (us, 256 | 1024 threads, correlation
+    // time 10 samples: 12832 series of 50: 81 | 316, of 400: 166 | 377; 1024
+    // of 2000: 57 | 71), and for series too short to feed more (one of 100: 23
+    // | 26); a few longer series want all lags at once (64 of 1024: 33 | 30).
+    const int cus = device_cus() > 0 ? device_cus() : 256;
+    if (n <= 128 || (n <= 2048 && R * S > cus)) launch(k_tau<256>, 256);
+    else launch(k_tau<kAT>, kAT);
     hip_check(hipGetLastError(), "tau launch");
     hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
 }

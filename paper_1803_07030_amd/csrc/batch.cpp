@@ -13,6 +13,7 @@
 
 #include "hsim_host.h"
 
+using hsim::device_cus;
 using hsim::Error;
 using hsim::hip_check;
 
@@ -38,14 +39,6 @@ int device_lds_limit()
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return 64 * 1024 - 1024;
     return v - 1024;
-}
-
-int device_cus()
-{
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    return v;
 }
 
 }  // namespace

@@ -25,6 +25,15 @@ inline void hip_check(hipError_t e, const char *what)
         throw Error(HSIM_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// Compute units of the current device (0 where there is none).
+inline int device_cus()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return v;
+}
+
 // Device allocation owned by a plan or batch.
 struct DevBuf {
     void *p = nullptr;

@@ -146,3 +146,26 @@ def test_multihist_without_room_for_copies(K):
         torch.cuda.empty_cache()
     assert got[1] == want[1] == 3
     assert np.array_equal(got[0], want[0]) and torch.equal(got[2], want[2])
+
+
+# Around the series lengths and numbers of series at which the blocks change
+# their size (64, 256 or 1024 threads).
+@pytest.mark.parametrize("R,S,n", [(1, 1, 256), (1, 1, 257), (2, 1, 1024), (1, 2, 1025), (301, 2, 50), (300, 1, 128),
+                                   (300, 1, 129), (300, 1, 257), (300, 1, 2048), (300, 1, 2049)])
+def test_block_sizes(R, S, n):
+    h, beta = _history(R, S, n + 1, seed=n)
+    slow = 20.0 * np.cos(np.arange(n + 1) * 2 * np.pi / max(0.3 * n, 4.0))
+    h[::2, ..., 0] += slow                       # windows up to the half length beside short ones
+    h[::2, ..., 3] += slow
+    d = torch.tensor(h, device="cuda")
+    out = hsim.hsim_analysis_thermal(d, 1, 64, beta, beta[..., None] * np.array([0.98, 1.0])).cpu().numpy()
+    taus = [hsim.hsim_analysis_tau(d, 1, obs) for obs in (0, 1)]
+    for r in range(0, R, max(1, R // 7)):
+        for s in range(S):
+            E, Mv = h[r, s, 1:, 0], h[r, s, 1:, 1:4]
+            for j, q in enumerate((0.98, 1.0)):
+                _close(out[r, s, j], A.thermal_array(A.reweight(E, Mv, 64, beta[r, s], q * beta[r, s])))
+            for (tau, win), x in zip(taus, (E, np.sqrt((Mv * Mv).sum(axis=1)))):
+                ref, w = A.tau_int(x)
+                assert int(win[r, s]) == w
+                _close(float(tau[r, s]), ref)
