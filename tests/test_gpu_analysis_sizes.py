@@ -169,3 +169,13 @@ def test_block_sizes(R, S, n):
                 ref, w = A.tau_int(x)
                 assert int(win[r, s]) == w
                 _close(float(tau[r, s]), ref)
+
+
+# A series whose mean is exact and whose deviations are 0: tau 1/2, window 0.
+@pytest.mark.parametrize("n", [2, 65, 300, 5000])
+@pytest.mark.parametrize("obs", [0, 1])
+def test_tau_of_a_constant_series(n, obs):
+    h = np.zeros((1, 2, n, 5))
+    h[..., 0], h[..., 1], h[..., 3] = 1.5, 3.0, 4.0            # |M| = 5
+    tau, win = hsim.hsim_analysis_tau(torch.tensor(h, device="cuda"), 0, obs)
+    assert torch.all(tau == 0.5) and torch.all(win == 0)
