@@ -1091,9 +1091,19 @@ bool run_persistent(hsim_batch b, const hsim::RunArgs &ra, hipStream_t st, uint3
 // registers and LDS covers double precision, spins in LDS, padded rows, one
 // or two classes of at most 256 sites (block_threads), the random move, no
 // cubic terms or spin lengths, no per-type output.
+//
+// It spends three threads per site of a class, so a CU keeps fewer replicas.
+// For classes of 65 to 128 sites two of its blocks (6 waves each, 3 per SIMD)
+// stand against four of k_block_sweep's, which is the faster one beyond 3
+// replicas per CU: SC 6^3, 50 MCS, us, pipe | sweep: 512 replicas 267 | 397,
+// 768: 392 | 393, 1024: 516 | 412, 2048: 1018 | 800.  Classes of more sites
+// gain at any number (SC 8^3 x 4096: 2898 | 3226), those of fewer lose 3% at
+// most, where the other kernel's blocks just fill the chip (SC 4^3 x 1536: 300
+// | 369, x 2048: 378 | 371, x 4096: 679 | 722).
 bool block_pipe_ok(hsim_batch b)
 {
     if (!b->f64 || !b->lds || b->block_threads > 256 || b->ellw == 0 || b->pol.n_types > 0 || b->type_mag) return false;
+    if (b->block_threads == 128 && b->R > 3 * device_cus()) return false;
     int64_t max_pad = 0;
     for (auto p : b->plans) {
         if (p->n > 0 && (p->ncol < 1 || p->ncol > 2)) return false;

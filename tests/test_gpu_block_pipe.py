@@ -58,3 +58,23 @@ def test_block_layout_equals_site_layout(case):
     for r, lat in enumerate(lats):
         scale = np.abs(lat.J).sum() / 2 + 2.0 * lat.n + 1.0
         assert float((h0[r, ..., :4] - h1[r, ..., :4]).abs().max()) <= 1e-12 * scale
+
+
+# Classes of 65 to 128 sites change the kernel beyond three replicas per CU.
+@pytest.mark.parametrize("more", [0, 1])
+def test_many_replicas_equal_site_layout(more):
+    R = 3 * torch.cuda.get_device_properties(0).multi_processor_count + more
+    plan = hsim.Plan(_with_terms(synth.sc_periodic(6), 4))
+    T = np.linspace(0.4, 2.5, R)[:, None]
+    got = []
+    for layout in (hsim.LAYOUT_BLOCK, hsim.LAYOUT_SITE):
+        b = hsim.Batch([plan] * R, seed=5, precision=hsim.FP64_EXACT, layout=layout).bind(1, 4)
+        b.bind_outputs(snapshots=True)
+        b.init_spins(hsim.INIT_RANDOM)
+        b.run(T, 0.2, recompute_every=2)
+        torch.cuda.synchronize()
+        assert b.status() == 0
+        got.append((b.history, b.snapshots))
+    (h0, s0), (h1, s1) = got
+    assert torch.equal(s0, s1) and torch.equal(h0[..., 4], h1[..., 4])
+    assert float((h0 - h1)[..., :4].abs().max()) <= 1e-12 * (4 * 216 + 1.0)   # bonds, k, B and M of 216 sites
