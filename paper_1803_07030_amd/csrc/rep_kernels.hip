@@ -649,57 +649,56 @@ __global__ __launch_bounds__(kRepThreads) void k_rep_phase(RepPhase ph, int t_of
 
 // Adaptive widths after MCS t_off of the sequence: the accepted adaptive
 // moves of every replica (record field 6 of all tiles of the MCS; whole
-// numbers, so any grouping gives the same sums) are summed by gridDim.x
-// blocks of 16 waves, a wave's lanes over replicas and the waves over tiles;
-// the last block to finish adds the blocks' sums and steers every width.
-// One block up to kSigmaOneBlock tiles, which needs no counter and no fence:
-// 261 tiles x 32 replicas took 9.9 us in 64 blocks whose lanes walked their
-// tiles one by one, 5.0 us in one block.
-constexpr int kSigmaWaves = 16, kSigmaOneBlock = 512, kSigmaBlocks = 16;
-static_assert(kSigmaBlocks <= kChunks, "the partial sums have kChunks rows");
+// numbers, so any grouping gives the same sums), a block per column of 64
+// replicas, its lanes over replicas and its 16 waves over the rows it adds.
+// Up to kSigmaOneBlock tiles that block reads the tiles' records itself; of
+// more, a launch before it adds them in chunks.  Adding the chunks in the
+// chunk launch's last block instead, behind a device-wide counter and its
+// fences, took 17 us per MCS where the two launches take 10.  50 MCS, us, one
+// launch | two: SC 18^3 (365 tiles) x 32 replicas 967 | 1010, x 64: 1150 |
+// 1162; SC 20^3 (500) x 32: 1042 | 1004, x 64: 1209 | 1151; SC 24^3 (864) x
+// 64: 1473 | 1357 (counter: 1750).
+constexpr int kSigmaWaves = 16, kSigmaOneBlock = 384;
 
-__global__ __launch_bounds__(kSigmaWaves * 64) void k_rep_sigma(RepLaneArgs a, int ntiles, int t_off, RunArgs ra)
+// Rows [b, e) of a replica column, stride doubles apart; valid in the first wave.
+__device__ __forceinline__ double sigma_rows(const double *rows, size_t stride, int b, int e, int r, int R)
 {
     __shared__ double lds[kSigmaWaves][64];
-    __shared__ int last;
-    const double *rec = rep_slot(ra, a, ntiles, t_off % ra.rec_win) + (size_t)6 * a.Rp;
-    const size_t stride = (size_t)kRecFields * a.Rp;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int nb = gridDim.x, k = blockIdx.x;
-    const int tb = (int)((int64_t)ntiles * k / nb), te = (int)((int64_t)ntiles * (k + 1) / nb);
-    auto adapt = [&](int r, double n) {
-        ra.sigma[r] = adapted_sigma(ra.sigma[r], n, ra.n_ad[r], ra.pol.sigma_min, ra.pol.sigma_max);
-    };
-    for (int r0 = 0; r0 < a.R; r0 += 64) {
-        const int r = r0 + lane;
-        double v = 0.0;
-        if (r < a.R)
+    double v = 0.0;
+    if (r < R)
 #pragma unroll 8
-            for (int tg = tb + w; tg < te; tg += kSigmaWaves) v += rec[(size_t)tg * stride + r];
-        lds[w][lane] = v;
-        __syncthreads();
-        if (w == 0 && r < a.R) {
-            double n = 0.0;
+        for (int q = b + w; q < e; q += kSigmaWaves) v += rows[(size_t)q * stride + r];
+    lds[w][lane] = v;
+    __syncthreads();
+    double n = 0.0;
+    if (w == 0)
 #pragma unroll
-            for (int q = 0; q < kSigmaWaves; ++q) n += lds[q][lane];
-            if (nb == 1) adapt(r, n);
-            else ra.sig_part[(size_t)k * a.Rp + r] = n;
-        }
-        __syncthreads();
-    }
-    if (nb == 1) return;
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) last = (atomicAdd(&ra.ctl->pad[2], 1u) == (uint32_t)nb - 1);
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    for (int r = threadIdx.x; r < a.R; r += blockDim.x) {
-        double n = 0.0;
-        for (int q = 0; q < nb; ++q) n += ra.sig_part[(size_t)q * a.Rp + r];
-        adapt(r, n);
-    }
-    if (threadIdx.x == 0) ra.ctl->pad[2] = 0;
+        for (int q = 0; q < kSigmaWaves; ++q) n += lds[q][lane];
+    return n;
+}
+
+// Chunk blockIdx.x of the tiles, replica column blockIdx.y.
+__global__ __launch_bounds__(kSigmaWaves * 64) void k_rep_sigma_part(RepLaneArgs a, int ntiles, int t_off, RunArgs ra)
+{
+    const double *rec = rep_slot(ra, a, ntiles, t_off % ra.rec_win) + (size_t)6 * a.Rp;
+    const int nb = gridDim.x, k = blockIdx.x, r = (threadIdx.x & 63) + 64 * blockIdx.y;
+    const int tb = (int)((int64_t)ntiles * k / nb), te = (int)((int64_t)ntiles * (k + 1) / nb);
+    const double n = sigma_rows(rec, (size_t)kRecFields * a.Rp, tb, te, r, a.R);
+    if (threadIdx.x < 64 && r < a.R) ra.sig_part[(size_t)k * a.Rp + r] = n;
+}
+
+// Replica column blockIdx.x; chunks: those of k_rep_sigma_part, 0 for the
+// tiles' records.
+__global__ __launch_bounds__(kSigmaWaves * 64) void k_rep_sigma(RepLaneArgs a, int ntiles, int chunks, int t_off,
+                                                                RunArgs ra)
+{
+    const int r = (threadIdx.x & 63) + 64 * blockIdx.x;
+    const double n = chunks > 0 ? sigma_rows(ra.sig_part, a.Rp, 0, chunks, r, a.R)
+                                : sigma_rows(rep_slot(ra, a, ntiles, t_off % ra.rec_win) + (size_t)6 * a.Rp,
+                                             (size_t)kRecFields * a.Rp, 0, ntiles, r, a.R);
+    if (threadIdx.x < 64 && r < a.R)
+        ra.sigma[r] = adapted_sigma(ra.sigma[r], n, ra.n_ad[r], ra.pol.sigma_min, ra.pol.sigma_max);
 }
 
 template <int KM, int FM, int W, int MAXD>
@@ -1119,8 +1118,13 @@ hipError_t launch_rep_phase(hipStream_t st, int kmode, int fmode, int colour, in
 hipError_t launch_rep_sigma(hipStream_t st, const RepLaneArgs &a, int ntiles, int t_off,
                             const RunArgs &ra)
 {
-    hipLaunchKernelGGL(k_rep_sigma, dim3(ntiles <= kSigmaOneBlock ? 1 : kSigmaBlocks), dim3(kSigmaWaves * 64), 0,
-                       st, a, ntiles, t_off, ra);
+    const unsigned cols = (unsigned)((a.R + 63) / 64);
+    const dim3 blk(kSigmaWaves * 64);
+    // a chunk gives every wave of its block eight tiles at least
+    const int chunks = ntiles <= kSigmaOneBlock ? 0 : std::min(kChunks, (ntiles + 8 * kSigmaWaves - 1) / (8 * kSigmaWaves));
+    if (chunks > 0)
+        hipLaunchKernelGGL(k_rep_sigma_part, dim3((unsigned)chunks, cols), blk, 0, st, a, ntiles, t_off, ra);
+    hipLaunchKernelGGL(k_rep_sigma, dim3(cols), blk, 0, st, a, ntiles, chunks, t_off, ra);
     return hipGetLastError();
 }
 

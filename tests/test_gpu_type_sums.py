@@ -53,3 +53,21 @@ def test_adaptive_widths_equal_the_site_layouts(L, R):
         got.append(b.sigma())
         assert b.status() == 0
     assert np.array_equal(got[0], got[1])
+
+
+# Just below and above the number of tiles one block adds by itself, and many
+# chunks of tiles, over one to three columns of replicas.
+@pytest.mark.parametrize("L,R", [(18, 70), (19, 33), (20, 150), (40, 66)])
+@pytest.mark.parametrize("launch", [hsim.LAUNCH_PLAIN, hsim.LAUNCH_GRAPH])
+def test_adaptive_widths_over_chunks_of_tiles(L, R, launch):
+    plan = hsim.Plan(synth.sc_periodic(L))
+    T = np.linspace(0.5, 1.4, R)[:, None] * np.ones((1, 2))
+    got = []
+    for layout in (hsim.LAYOUT_REPLICA, hsim.LAYOUT_SITE):
+        b = hsim.Batch([plan] * R, seed=3, layout=layout).bind(2, 3)
+        b.set_policies([(hsim.POLICY_ADAPTIVE, 0.5)])
+        b.init_spins(hsim.INIT_COLD_Z)
+        b.run(T, 0.0, launch=launch if layout == hsim.LAYOUT_REPLICA else hsim.LAUNCH_PLAIN)
+        got.append(b.sigma())
+        assert b.status() == 0
+    assert np.array_equal(got[0], got[1])
