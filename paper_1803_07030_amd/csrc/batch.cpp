@@ -297,17 +297,29 @@ hsim_batch batch_create_impl(int32_t R, const hsim_plan *plans, uint64_t seed,
             // lattices fill the GPU.  Measured on SC L^3 x 64 replicas (us per
             // phase): L = 56: 45.8 (32), 54.8 (16); L = 48: 37.4 (32), 34.0
             // (16), 28.1 (8); L = 32: 17.6 (16), 12.6 (8), 11.9 (4); 16 sites
-            // per wave was never the best and is not used.  Spin sets beyond
-            // the last-level cache (256 MB) take 8 as well: shorter tiles keep
-            // the rows that the sites in flight share closer together in
-            // time (us per MCS, 32 | 8: L = 66 (221 MB) 162 | 165, 68 (241 MB)
-            // 223 | 193, 80 (393 MB) 394 | 350, 96 (679 MB) 611 | 579); the
-            // largest go back to 32 (L = 128, 1.6 GB: 1281 | 1365).
+            // per wave was never the best and is not used.  Between two sizes
+            // of the spin set 8 is best as well: tables and records share the
+            // 256 MiB of the last-level cache with the spins, and beyond what
+            // fits shorter tiles keep the rows that the sites in flight share
+            // closer together in time; of the largest sets little stays
+            // cached either way, and 32 saves records.  The lines, from us
+            // per MCS (32 | 8 sites; MB of spins):
+            //   64 replicas: L = 66 (221) 164 | 169, 67 (231) 234 | 203, 68
+            //     (241) 222 | 191, 80 (393) 394 | 350, 96 (679) 638 | 601, 112
+            //     (1079) 1011 | 966, 120 (1327) 1164 | 1212, 128 (1611) 1281 |
+            //     1365; 512 replicas: L = 34 (241) 227 | 198, 48 (679) 652 | 639;
+            //   more columns: 1024 replicas, L = 28 (270) 319 | 297, 32 (403)
+            //     465 | 489; 2048, L = 22 (262) 326 | 287, 24 (340) 356 | 415;
+            //   32-lane rows, whose two groups per wave take their sites one
+            //     at a time: L = 64 (101) 73 | 76, 72 (143) 143 | 105, 80 (197)
+            //     185 | 147, 110 (511) 599 | 534, 120 (664) 693 | 687, 128 (805)
+            //     795 | 832.
             // hsim_autotune may pick another of these shapes.
-            const int64_t spin_bytes = 12 * max_n * b->Rp;
+            const int64_t spin_mb = 12 * max_n * b->Rp / 1000000;
+            const int64_t lo = b->Rp >= 64 ? 226 : 120, hi = b->Rp < 64 ? 730 : b->Rp <= 512 ? 1200 : 300;
             const int cus = device_cus() > 0 ? device_cus() : 256;
             int spw = hsim::kRepSitesPerWave;
-            if (spin_bytes > ((int64_t)230 << 20) && spin_bytes < ((int64_t)1 << 30) && b->Rp % 64 == 0)
+            if (spin_mb >= lo && spin_mb < hi)
                 spw = 8;
             else if (rep_phase_blocks(b, spw) < 2 * (int64_t)cus)
                 for (int cand : {8, 4})
