@@ -212,7 +212,7 @@ struct hsim_batch_s {
     double *h_stage = nullptr;              // pinned staging of beta and bfield
     hipEvent_t stage_done = nullptr;
 
-    // GRAPH launches: the instantiated graph of one recompute period, kept
+    // GRAPH launches: the instantiated graph of a stretch of MCS, kept
     // across calls while the captured arguments stay the same; captured on a
     // private stream (nothing runs there) and replayed on the caller's
     hipGraph_t g_graph = nullptr;
@@ -220,6 +220,7 @@ struct hsim_batch_s {
     hipStream_t g_cap = nullptr;
     hipEvent_t g_done = nullptr;          // recorded after the last enqueued replay
     std::vector<unsigned char> g_key;
+    std::vector<unsigned char> g_once;    // key of the last one-step call that went plain
     void drop_graph();                    // waits for enqueued replays, then frees
 
     // tuning

@@ -5,6 +5,7 @@ for bit, with the adaptive move among the policies."""
 import numpy as np
 import pytest
 import torch
+from torch.profiler import ProfilerActivity, profile
 
 import synth
 from paper_1803_07030_amd import hsim
@@ -33,5 +34,28 @@ def test_graph_units_equal_plain_launches(layout, R, steps, M, P):
         assert b.status() == 0
         got.append([b.history, b.type_mag, b.snapshots, torch.cat([b.spins_user(r) for r in range(R)]),
                     torch.tensor(b.sigma())])
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("M,P,graphs", [(130, 100, 1), (512, 0, 1), (127, 0, 0)])
+def test_loop_of_one_step_calls_replays_its_graph(M, P, graphs):
+    # a call of one step goes plain; the same call again replays the step
+    plan = hsim.Plan(synth.sc_periodic(6))
+    T = np.linspace(0.6, 2.0, 20)[:, None]
+    got = []
+    for launch in (hsim.LAUNCH_PLAIN, hsim.LAUNCH_GRAPH):
+        b = hsim.Batch([plan] * 20, seed=4, layout=hsim.LAYOUT_REPLICA).bind(1, M)
+        b.init_spins(hsim.INIT_RANDOM)
+        for _ in range(2):
+            b.run(T, 0.1, recompute_every=P, launch=launch)
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+            b.run(T, 0.1, recompute_every=P, launch=launch)
+            torch.cuda.synchronize()
+        seen = {e.key: e.count for e in p.key_averages()}
+        assert seen.get("hipGraphLaunch", 0) == (graphs if launch == hsim.LAUNCH_GRAPH else 0), seen
+        assert b.status() == 0
+        got.append([b.history, torch.cat([b.spins_user(r) for r in range(20)])])
     for x, y in zip(*got):
         assert torch.equal(x, y)
