@@ -853,9 +853,11 @@ bool site_plain(hsim_batch b)
 
 // Site layout, one group's MCS t of a sequence: the energy recompute when
 // due, the colour phases below c_tail, the finish launch (trailing classes
-// and history) of the group's replicas.
+// and history) of the group's replicas.  plain: site_plain(b), which walks the
+// plans, so it is asked once per sequence.
 template <typename F>
-void enqueue_site_mcs(hsim_batch b, const hsim::RunArgs &ra, int g, int t, F efull_mask, hipStream_t st)
+void enqueue_site_mcs(hsim_batch b, const hsim::RunArgs &ra, bool plain, int g, int t, F efull_mask,
+                      hipStream_t st)
 {
     const auto *reps = (const hsim::RepDesc *)b->d_reps.p;
     const auto *tiles = (const hsim::Tile *)b->d_tiles.p;
@@ -866,7 +868,6 @@ void enqueue_site_mcs(hsim_batch b, const hsim::RunArgs &ra, int g, int t, F efu
                                           t, ra),
                   "efull launch");
     const bool timed = b->time_every > 0 && t % b->time_every == 0;
-    const bool plain = site_plain(b);
     const auto *rlist = b->ngroups > 1 ? (const int32_t *)b->d_grp_reps[g].p : nullptr;
     for (int c = 0; c < b->c_tail; ++c) {
         PhaseTimer pt(b, st, timed && to[c + 1] > to[c], c, b->gunits[g][c]);
@@ -903,6 +904,7 @@ void enqueue_site_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F e
                            hipStream_t st, const StepEnd &ends, bool split)
 {
     if (count <= 0) return;
+    const bool plain = site_plain(b);
     if (split && b->ngroups > 1) {
         if (!b->gfork) {
             hip_check(hipEventCreateWithFlags(&b->gfork, hipEventDisableTiming), "hipEventCreate");
@@ -914,13 +916,13 @@ void enqueue_site_sequence(hsim_batch b, const hsim::RunArgs &ra, int count, F e
         hip_check(hipEventRecord(b->gfork, st), "hipEventRecord");
         for (int g = 0; g < 2; ++g) {
             hip_check(hipStreamWaitEvent(b->gstream[g], b->gfork, 0), "hipStreamWaitEvent");
-            for (int t = 0; t < count; ++t) enqueue_site_mcs(b, ra, g, t, efull_mask, b->gstream[g]);
+            for (int t = 0; t < count; ++t) enqueue_site_mcs(b, ra, plain, g, t, efull_mask, b->gstream[g]);
             hip_check(hipEventRecord(b->gjoin[g], b->gstream[g]), "hipEventRecord");
             hip_check(hipStreamWaitEvent(st, b->gjoin[g], 0), "hipStreamWaitEvent");
         }
     } else {
         for (int t = 0; t < count; ++t) {
-            for (int g = 0; g < b->ngroups; ++g) enqueue_site_mcs(b, ra, g, t, efull_mask, st);
+            for (int g = 0; g < b->ngroups; ++g) enqueue_site_mcs(b, ra, plain, g, t, efull_mask, st);
             enqueue_outputs(b, ra, t, ends, st);
         }
     }
