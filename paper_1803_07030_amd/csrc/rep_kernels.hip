@@ -52,7 +52,6 @@ __device__ __forceinline__ void accumulate(double (&acc)[6], bool ok, bool live,
 template <int KM, int FM, bool UNI = false>
 struct RepSite {
     float k, ex, ey, ez, nx, ny, nz;
-    RepSite() = default;
     template <typename T>
     __device__ __forceinline__ static T ld(const T *p, int64_t i)
     {
@@ -641,7 +640,7 @@ __global__ __launch_bounds__(kRepThreads) void k_rep_phase(RepPhase ph, int t_of
                  "s"(a.ss), "s"(a.spw), "s"(a.masked_store), "s"(a.tord), "s"(ra.ctl), "s"(ra.beta),
                  "s"(ra.bfield), "s"(ra.partials), "s"(ra.seed), "s"(ra.M), "s"(ra.S_hist), "s"(ra.rec_win));
     if constexpr (KM == K_SITE) asm volatile("" ::"s"(a.k), "s"(a.ax));
-        const uint32_t g = cload(&ra.ctl->g, 0) + (uint32_t)t_off;   // (no launch of the sweep writes it)
+    const uint32_t g = cload(&ra.ctl->g, 0) + (uint32_t)t_off;   // (no launch of the sweep writes it)
     const int u = xcd_tile(blockIdx.x, ph.nt);
     rep_tile<KM, FM, W, MAXD, VAR>(a, ph, a.tord ? cload(a.tord, ph.tile0 + u) : u, blockIdx.y, g, ra,
                                    rep_slot(ra, a, ntiles, t_off % ra.rec_win), red);
@@ -1080,9 +1079,9 @@ hipError_t launch_to_user_rep(hipStream_t st, const RepLaneArgs &a, int rep, dou
 
 static int lane_width(const RepLaneArgs &a) { return a.Rp % 64 == 0 ? 64 : 32; }
 
-// Rows padded to 6 or 8 slots use the fixed-width pair updates (the plan
-// pads to 6 when every row has at most 6 entries, else to 8); wider rows the
-// generic row walk.
+// Rows padded to 6 or 8 slots use the fixed-width updates, one site at a time
+// (rep_step_uniform, rep_step_group; the plan pads to 6 when every row has at
+// most 6 entries, else to 8); wider rows the generic row walk.
 #define HSIM_DISPATCH_D(ELLW_, ...)                                                             \
     do {                                                                                         \
         if ((ELLW_) == 6) { constexpr int MAXD = 6; __VA_ARGS__; }                               \
