@@ -27,6 +27,7 @@
 // groups and passes in order.  Batches larger than the plan's pass size run
 // in passes over a fixed scratch (no allocation per call).
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -693,33 +694,73 @@ hipError_t launch_site_kernel(hipStream_t st, const EnergyArgs &a, const EnergyL
     return hipGetLastError();
 }
 
-// Configurations per work item of a pass of cnt: the largest power of two, 32
-// to kEU, that gives kEnergyItems items (4 per CU), and never more groups
-// than the scratch holds (L.groups).  A call of a few groups of 32 leaves most
-// of the chip idle while each block walks its group two configurations at a
-// time.  Forward and backward, us, groups of 32 | by this rule: 75
-// configurations of a film of 16,700 sites 75.9 | 48.6 (with the weights and
-// the conversion of the states); SC 16^3 x 64 50.0 | 29.2; SC 20^3 x 300 in
-// double precision 89.1 | 66.4 (72.3 with 512 items); from 1024 items of 32
-// on, as SC 32^3 x 1024, the rule changes nothing.
+// Configurations per work item of a pass of cnt, with never more groups than
+// the scratch holds (L.groups).
+//
+// Few tiles: the largest power of two, 32 to kEU, that gives kEnergyItems items
+// (4 per CU).  A call of a few groups of 32 leaves most of the chip idle while
+// each block walks its group two configurations at a time.  Forward and
+// backward, us, groups of 32 | by this rule: 75 configurations of a film of
+// 16,700 sites 75.9 | 48.6 (with the weights and the conversion of the
+// states); SC 16^3 x 64 50.0 | 29.2; SC 20^3 x 300 in double precision 89.1 |
+// 66.4 (72.3 with 512 items).
+//
+// From 192 tiles on (96 for rows of 8) one group fills most of the chip, and
+// more groups than run at once only read the lattice's tables again, which a
+// block does before its first configuration at the price of about 4.  So the
+// groups are those that make rounds of resident blocks (by the kernels'
+// registers) x (configurations + 4) least, all of one size, as a smaller last
+// group would leave the XCDs that have it idle.  Backward, us, groups of 32 |
+// 1024 items | so: SC 48^3 x 17 in double precision 35.8 | 48.4 | 35.7, SC
+// 40^3 x 33 in single 40.7 | 29.5 | 25.4, BCC 30^3 x 17 in double 28.2 | 39.1 |
+// 28.1.  Past two rounds of full groups the size changes little.
+//
+// Rows of any length from 96 tiles on: every XCD reads every group's current
+// configuration, so groups in flight beyond what an L2 holds cost more than
+// idle CUs.  Forward, us, FCC 20^3 (125 tiles) in double precision, 32 | 1024
+// items | so: 64 configurations 206 | 322 | 161, 130: 329 | 664 | 329.
 constexpr int64_t kEnergyItems = 1024;
-int group_size(const EnergyLayout &L, int cnt)
+int group_size(const EnergyLayout &L, int cnt, bool f64, bool bwd)
 {
-    int g = kEG;
-    while (g > kEU && (int64_t)((cnt + g - 1) / g) * L.ntile < kEnergyItems && (cnt + g / 2 - 1) / (g / 2) <= L.groups)
-        g /= 2;
-    return g;
+    const int w = L.ell_w, least = (cnt + kEG - 1) / kEG;
+    const bool ell = w == 6 || w == 8;
+    if (L.ntile < (w == 6 ? 192 : 96)) {
+        int g = kEG;
+        while (g > kEU && (int64_t)((cnt + g - 1) / g) * L.ntile < kEnergyItems &&
+               (cnt + g / 2 - 1) / (g / 2) <= L.groups)
+            g /= 2;
+        return g;
+    }
+    if (!ell) {
+        if ((int64_t)least * L.ntile > 512) return kEG;
+        const int groups = std::max(least, std::min({(f64 ? 512 : 768) / L.ntile, (cnt + 1) / 2, L.groups}));
+        return (cnt + groups - 1) / groups;
+    }
+    const int resident = bwd ? (f64 ? 512 : w == 6 ? 1024 : 768) : f64 ? (w == 6 ? 1024 : 512) : w == 6 ? 2048 : 1536;
+    if ((int64_t)least * L.ntile > 2 * resident) return kEG;
+    int best = kEG;
+    double cost = INFINITY;
+    for (int groups = least; groups <= std::max(least, std::min((cnt + 3) / 4, L.groups)); ++groups) {
+        const int g = ((cnt + groups - 1) / groups + kEU - 1) / kEU * kEU;
+        const double waves = (double)((cnt + g - 1) / g) * L.ntile / resident;
+        const double c = std::ceil(waves) * (g + 4);
+        if (c < cost) {
+            cost = c;
+            best = g;
+        }
+    }
+    return best;
 }
 
 // The pass [b0, b0 + cnt) of the batch: the arguments with the spins (and
 // their gradients) moved to the pass's first configuration.
-EnergyArgs pass_args(const EnergyArgs &a, const EnergyLayout &L, bool f64, int b0, int cnt)
+EnergyArgs pass_args(const EnergyArgs &a, const EnergyLayout &L, bool f64, bool bwd, int b0, int cnt)
 {
     EnergyArgs p = a;
     const size_t es = f64 ? 8 : 4;
     p.S = (const char *)a.S + (size_t)b0 * 3 * a.n * es;
     p.batch = cnt;
-    p.eg = group_size(L, cnt);
+    p.eg = group_size(L, cnt, f64, bwd);
     return p;
 }
 
@@ -731,7 +772,7 @@ hipError_t launch_energy_forward(hipStream_t st, bool f64, const EnergyArgs &a,
     if (L.pass_cfg < 1) return hipErrorInvalidValue;
     for (int b0 = 0; b0 < a.batch; b0 += L.pass_cfg) {
         const int cnt = std::min(L.pass_cfg, a.batch - b0);
-        const EnergyArgs p = pass_args(a, L, f64, b0, cnt);
+        const EnergyArgs p = pass_args(a, L, f64, false, b0, cnt);
         double *partE = scratch + L.off_partE;
         hipError_t e = f64 ? launch_site_kernel<double, false>(st, p, L, nullptr, nullptr, partE, nullptr, nullptr, nullptr)
                            : launch_site_kernel<float, false>(st, p, L, nullptr, nullptr, partE, nullptr, nullptr, nullptr);
@@ -757,7 +798,7 @@ hipError_t launch_energy_backward(hipStream_t st, bool f64, const EnergyArgs &a,
     for (int b0 = 0; b0 < a.batch; b0 += L.pass_cfg) {
         const int cnt = std::min(L.pass_cfg, a.batch - b0);
         const int first = b0 == 0, last = b0 + cnt >= a.batch;
-        const EnergyArgs p = pass_args(a, L, f64, b0, cnt);
+        const EnergyArgs p = pass_args(a, L, f64, true, b0, cnt);
         void *gSp = gS ? (char *)gS + (size_t)b0 * 3 * a.n * es : nullptr;
         double *pk = gk ? partK : nullptr, *pj = gJ ? partJ : nullptr;
         hipError_t e = f64 ? launch_site_kernel<double, true>(st, p, L, gE + b0, (double *)gSp, nullptr, partB, pk, pj)

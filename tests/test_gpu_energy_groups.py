@@ -66,3 +66,15 @@ def test_splits_match_the_formulas(dtype, kind, L, batch):
     assert float((gJ.double() - rJ).abs().max()) <= bJ
     assert float((gk.double() - rk).abs().max()) <= bk
     assert abs(float(gB) - float(rB)) <= bB
+
+
+# From 192 tiles of 256 sites on (96 on rows beyond 6) groups are formed by the
+# blocks that run at once: ragged batches of one group to several, and past
+# two rounds of them.
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("batch", [3, 17, 50, 170])
+@pytest.mark.parametrize("kind,L,degree", [("sc", 37, 6), ("tree", 25000, 8), ("tree", 25000, 12)])
+def test_groups_of_many_tiles_match_the_formulas(monkeypatch, dtype, kind, L, degree, batch):
+    tree = synth.random_tree
+    monkeypatch.setattr(synth, "random_tree", lambda n, seed, max_degree: tree(n, seed=seed, max_degree=degree))
+    test_splits_match_the_formulas(dtype, kind, L, batch)
