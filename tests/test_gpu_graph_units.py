@@ -54,6 +54,8 @@ def test_loop_of_one_step_calls_replays_its_graph(M, P, graphs):
             b.run(T, 0.1, recompute_every=P, launch=launch)
             torch.cuda.synchronize()
         seen = {e.key: e.count for e in p.key_averages()}
+        if "hipLaunchKernel" not in seen:
+            pytest.skip("the profiler records no launches here")
         assert seen.get("hipGraphLaunch", 0) == (graphs if launch == hsim.LAUNCH_GRAPH else 0), seen
         assert b.status() == 0
         got.append([b.history, torch.cat([b.spins_user(r) for r in range(20)])])
