@@ -727,8 +727,8 @@ void analysis_thermal_impl(const double *d_hist, int32_t R, int32_t S, int32_t M
     const int n = M - m0;
     const dim3 grid((unsigned)T, (unsigned)n_eval);
     auto launch = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, d_hist, M, m0, n, (double)n_sites, (const double *)d_tab.p, bt,
-                           n_eval, d_out);
+        hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, d_hist, M, m0, n, (double)n_sites,
+                           (const double *)d_tab.p, bt, n_eval, d_out);
     };
     if (n <= 4 * 64) launch(arg ? k_thermal<4, 64, true> : k_thermal<4, 64, false>, 64);
     else if (n <= 4 * 256) launch(arg ? k_thermal<4, 256, true> : k_thermal<4, 256, false>, 256);
